@@ -137,13 +137,15 @@ __global__ __launch_bounds__(256) void density_from_parts_kernel(double* rho, co
   }
 }
 
-__global__ void twiddle_kernel(double2* w, int M)
+__global__ void twiddle_kernel(double2* w, double* s2, int M, double d)
 {
   const int k = blockIdx.x * blockDim.x + threadIdx.x;
   if (k >= M) return;
   double sn, cs;
   sincospi(2.0 * (double)k / (double)M, &sn, &cs);
   w[k] = make_double2(cs, -sn);  // exp(-2 pi i k / M)
+  const double h = sinpi((double)k / M);
+  s2[k] = h * h / (d * d);
 }
 
 // One workgroup per line of the axis; lanes compute frequencies.
@@ -274,6 +276,283 @@ __global__ __launch_bounds__(64) void fft_kernel(double2* data, long long inner,
   }
 }
 
+// ---- the whole gravity solve of a small grid in one workgroup -----------------
+// For transform grids that fit the LDS twice, one workgroup does all of
+// Eqs. (18)-(22): the density (from rho, or from per-chunk partial sums), the
+// forward transforms, the Green's function, the inverse transforms and the
+// two-point gradient, with the grid in LDS throughout; the reverse mode's
+// transposed map takes the same way. The separate kernels take eleven
+// launches of 2 to 5 us each for arithmetic of under a microsecond: launches
+// bound them. This one is bound by latency: the chain of barriers, and
+// fetching code that runs once. So both directions of the transform and all
+// axes go through one copy of the code, loops stay rolled, and what the host
+// can divide comes divided. 8^3 periodic (nine launches, about 30 us, before)
+// takes 8.5 us, 16^3 (55 us before) 21 us, its transpose 23 us.
+constexpr int SG_TW = 3 * 128;   // twiddles of the three axes (accepted lengths)
+
+// R-point DFT of v in place; sg 1 forward, -1 inverse
+template <int R>
+__device__ __forceinline__ void dft_r(double2 (&v)[R], double sg)
+{
+  if constexpr (R == 4) {
+    const double2 s0 = make_double2(v[0].x + v[2].x, v[0].y + v[2].y), d0 = make_double2(v[0].x - v[2].x, v[0].y - v[2].y);
+    const double2 s1 = make_double2(v[1].x + v[3].x, v[1].y + v[3].y);
+    const double2 d1 = make_double2(sg * (v[1].y - v[3].y), -sg * (v[1].x - v[3].x));   // -+i (v1 - v3)
+    v[0] = make_double2(s0.x + s1.x, s0.y + s1.y);
+    v[1] = make_double2(d0.x + d1.x, d0.y + d1.y);
+    v[2] = make_double2(s0.x - s1.x, s0.y - s1.y);
+    v[3] = make_double2(d0.x - d1.x, d0.y - d1.y);
+  } else if constexpr (R == 2) {
+    const double2 d = make_double2(v[0].x - v[1].x, v[0].y - v[1].y);
+    v[0] = make_double2(v[0].x + v[1].x, v[0].y + v[1].y);
+    v[1] = d;
+  } else {
+    const double h3 = sg * 0.86602540378443864676;   // sqrt(3) / 2
+    const double2 s = make_double2(v[1].x + v[2].x, v[1].y + v[2].y);
+    const double2 m = make_double2(v[0].x - 0.5 * s.x, v[0].y - 0.5 * s.y);
+    const double2 e = make_double2(h3 * (v[1].y - v[2].y), -h3 * (v[1].x - v[2].x));
+    v[0] = make_double2(v[0].x + s.x, v[0].y + s.y);
+    v[1] = make_double2(m.x + e.x, m.y + e.y);
+    v[2] = make_double2(m.x - e.x, m.y - e.y);
+  }
+}
+
+// One Stockham stage along an axis of the LDS grid (see fft_kernel for the
+// indexing): element j of line (o, c) at (o M + j) inner + c. sg is 1 forward,
+// -1 inverse. The stage's integers and their reciprocals come from the host:
+// as divisions here they took three times as long as the butterflies.
+template <int R>
+__device__ __forceinline__ void sg_stage(const double2* a, double2* b, int tot, const SgStage& p, double sg,
+                                         const double2* w)
+{
+  const int inner = p.inner, step = p.step, ns = p.ns;
+#pragma unroll 1
+  for (int u = threadIdx.x; u < tot / R; u += blockDim.x) {
+    // lane -> (o, t, c); the lines' c count is that of the unpadded grid
+    const int q1 = div_small(u, p.cols, p.r_cols), cu = u - q1 * p.cols;
+    const int o = div_small(q1, step, p.r_step), t = q1 - o * step;
+    const int crow = div_small(cu, p.row, p.r_row), c = cu + crow * p.pad;
+    const int tq = div_small(t, ns, p.r_ns), k = t - tq * ns;
+    const int ob = o * p.outer + c;
+    double2 v[R];
+#pragma unroll
+    for (int r = 0; r < R; r++) {
+      const double2 x = a[ob + (t + r * step) * inner];
+      double2 tw = w[p.woff + r * k * p.tws];
+      tw.y *= sg;
+      v[r] = r ? cmul(x, tw) : x;
+    }
+    double2* d = b + ob + (tq * ns * R + k) * inner;
+    const int ds = ns * inner;
+    dft_r<R>(v, sg);
+#pragma unroll
+    for (int q = 0; q < R; q++) d[q * ds] = v[q];
+  }
+}
+
+// Lines of M <= 16 cells: one lane transforms a whole line in registers, in
+// place in LDS, with every index a constant: two stages (fours, then a two or
+// a three) without a barrier between them.
+template <int M>
+__device__ __forceinline__ void sg_lines(double2* a, const SgStage& p_, double sg, const double2* w)
+{
+  const int inner = p_.inner;
+  constexpr int R1 = M % 4 == 0 ? 4 : (M % 2 == 0 ? 2 : 3), R2 = M / R1;   // M = R1 R2, R2 = 1, 2, 3 or 4
+  static_assert(R2 <= 4, "two stages");
+#pragma unroll 1
+  for (int l = threadIdx.x; l < p_.step; l += blockDim.x) {
+    const int o = div_small(l, p_.cols, p_.r_cols), cu = l - o * p_.cols;
+    double2* p = a + o * p_.outer + cu + div_small(cu, p_.row, p_.r_row) * p_.pad;
+    double2 x[M];
+#pragma unroll
+    for (int j = 0; j < M; j++) x[j] = p[j * inner];
+    // first stage: R2 transforms of R1 values R2 apart
+#pragma unroll
+    for (int t = 0; t < R2; t++) {
+      double2 v[R1];
+#pragma unroll
+      for (int r = 0; r < R1; r++) v[r] = x[t + r * R2];
+      dft_r<R1>(v, sg);
+#pragma unroll
+      for (int q = 0; q < R1; q++) x[t + q * R2] = v[q];
+    }
+    // second stage: output q R1 + k = sum over t of w^(t (k + q R1)) x[t + k R2]
+    if constexpr (R2 > 1) {
+#pragma unroll
+      for (int k = 0; k < R1; k++) {
+        double2 v[R2];
+#pragma unroll
+        for (int t = 0; t < R2; t++) {
+          v[t] = x[t + k * R2];
+          if (t * k != 0) {
+            double2 tw = w[t * k];
+            tw.y *= sg;
+            v[t] = cmul(v[t], tw);
+          }
+        }
+        dft_r<R2>(v, sg);
+#pragma unroll
+        for (int q = 0; q < R2; q++) p[(k + q * R1) * inner] = v[q];
+      }
+    } else {
+#pragma unroll
+      for (int k = 0; k < R1; k++) p[k * inner] = x[k];
+    }
+  }
+}
+
+template <int CAP, int THREADS, bool ADJ>
+__global__ __launch_bounds__(THREADS) void gravity_small_kernel(SmallGravity q)
+{
+  __shared__ double2 buf[2 * CAP];
+  __shared__ double2 w[SG_TW];
+  double2 *a = buf, *b = buf + CAP;
+  const int t = threadIdx.x;
+  const int g0 = q.g.m[0], g1 = q.g.m[1], g2 = q.g.m[2], tot = g0 * g1 * g2;
+  // rows of an odd number of 16-byte values: lanes one row apart, and lanes
+  // along a row, take distinct banks
+  const int p2 = g2 | 1;
+  const int n0 = q.n.m[0], n1 = q.n.m[1], n2 = q.n.m[2], np = n0 * n1 * n2;
+  const float rg2 = q.rg2, rg1 = q.rg1, rn2 = q.rn2, rn1 = q.rn1;
+  // twiddles of the three axes, one after the other
+  for (int k = t; k < g0 + g1 + g2; k += THREADS)
+    w[k] = k < g0 ? q.tw[0][k] : (k < g0 + g1 ? q.tw[1][k - g0] : q.tw[2][k - g0 - g1]);
+  if constexpr (!ADJ) {
+    double* rs = reinterpret_cast<double*>(b);   // the density, before the transforms need b
+    if (q.part) {
+      // rho[cell] = dv3 sum_k part[k np + cell]: groups of threads take every
+      // G-th chunk, then the G sums of a cell are added in order of the group
+      const int G = q.groups, grp = G > 1 ? t / np : 0, nchunk = (int)q.nchunk;
+#pragma unroll 1
+      for (int cell = t - grp * np; cell < np && grp < G; cell += THREADS) {
+        double x[8] = {};
+        int k = grp;
+        const double* p = q.part + cell;
+#pragma unroll 1
+        for (; k + 7 * G < nchunk; k += 8 * G) {
+#pragma unroll
+          for (int i = 0; i < 8; i++) x[i] += p[(k + i * G) * np];
+        }
+#pragma unroll 1
+        for (; k < nchunk; k += G) x[0] += p[k * np];
+        rs[grp * np + cell] = (((x[0] + x[1]) + (x[2] + x[3])) + ((x[4] + x[5]) + (x[6] + x[7]))) * q.dv3;
+      }
+      __syncthreads();
+      if (G > 1) {                               // then np < THREADS: one cell per lane
+        double s = 0.0;
+        if (t < np) {
+#pragma unroll 1
+          for (int k = 0; k < G; k++) s += rs[k * np + t];
+        }
+        __syncthreads();
+        if (t < np) rs[t] = s;
+        __syncthreads();
+      }
+    }
+    const double* src = q.part ? rs : q.rho;
+#pragma unroll 1
+    for (int s = t; s < tot; s += THREADS) {
+      const int q1 = div_small(s, g2, rg2), i2 = s - q1 * g2;
+      int at = s;
+      bool in = true;
+      if (q.isolated) {
+        const int i0 = div_small(q1, g1, rg1), i1 = q1 - i0 * g1;
+        in = i0 < n0 && i1 < n1 && i2 < n2;
+        at = (i0 * n1 + i1) * n2 + i2;
+      }
+      a[q1 * p2 + i2] = make_double2(in ? src[at] : 0.0, 0.0);
+    }
+  } else {
+    // Transpose of potential -> acceleration at the grid place p: along axis l
+    // the acceleration of cell p - 1 took phi(p) with -1/(2 d_l), that of p + 1
+    // with +1/(2 d_l). The ghost layer's places are those mod g (images of the
+    // periodic grid, the doubled grid's far end of the isolated one), cells
+    // beyond n hold nothing.
+#pragma unroll 2
+    for (int s = t; s < tot; s += THREADS) {
+      const int q1 = div_small(s, g2, rg2), i2 = s - q1 * g2, i0 = div_small(q1, g1, rg1), i1 = q1 - i0 * g1;
+      auto diff = [&](int l, int i, int n, int g, int st, bool in) {
+        const double* p = q.lam_a + (l * np + (i0 * n1 + i1) * n2 + i2 - i * st);
+        const int hi = i + 1 == g ? 0 : i + 1, lo = i == 0 ? g - 1 : i - 1;
+        const double a = in && hi < n ? p[hi * st] : 0.0, b = in && lo < n ? p[lo * st] : 0.0;
+        return a - b;
+      };
+      const bool in0 = i0 < n0, in1 = i1 < n1, in2 = i2 < n2;
+      const double v0 = diff(0, i0, n0, g0, n1 * n2, in1 && in2), v1 = diff(1, i1, n1, g1, n2, in0 && in2),
+                   v2 = diff(2, i2, n2, g2, 1, in0 && in1);
+      a[q1 * p2 + i2] = make_double2(v0 * q.h[0] + v1 * q.h[1] + v2 * q.h[2], 0.0);
+    }
+  }
+  __syncthreads();
+#pragma unroll 1
+  for (int dir = 0; dir < 2; dir++) {
+    if (dir == 1) {
+#pragma unroll 2
+      for (int s = t; s < tot; s += THREADS) {
+        const int q1 = div_small(s, g2, rg2), at = q1 * p2 + (s - q1 * g2);
+        a[at] = cmul(a[at], q.kspec[s]);
+      }
+      __syncthreads();
+    }
+    const double sg = dir == 0 ? 1.0 : -1.0;
+#pragma unroll 1
+    for (int st = 0; st < q.nstage; st++) {
+      const SgStage& p = q.stage[st];
+      switch (p.R) {
+        case 2: sg_stage<2>(a, b, tot, p, sg, w); break;
+        case 3: sg_stage<3>(a, b, tot, p, sg, w); break;
+        case 4: sg_stage<4>(a, b, tot, p, sg, w); break;
+        // whole lines in registers, coded as 100 + M
+        case 102: sg_lines<2>(a, p, sg, w + p.woff); break;
+        case 103: sg_lines<3>(a, p, sg, w + p.woff); break;
+        case 104: sg_lines<4>(a, p, sg, w + p.woff); break;
+        case 106: sg_lines<6>(a, p, sg, w + p.woff); break;
+        case 108: sg_lines<8>(a, p, sg, w + p.woff); break;
+        case 112: sg_lines<12>(a, p, sg, w + p.woff); break;
+        default: sg_lines<16>(a, p, sg, w + p.woff); break;
+      }
+      __syncthreads();
+      if (p.R <= 4) {
+        double2* x = a;
+        a = b;
+        b = x;
+      }
+    }
+  }
+  const double scale = q.scale;
+  if constexpr (ADJ) {
+#pragma unroll 1
+    for (int s = t; s < np; s += THREADS) {
+      const int q1 = div_small(s, n2, rn2), i2 = s - q1 * n2, i0 = div_small(q1, n1, rn1), i1 = q1 - i0 * n1;
+      q.radj[s] = a[(i0 * g1 + i1) * p2 + i2].x * scale;
+    }
+    return;
+  }
+  if (q.accel) {
+#pragma unroll 1
+    for (int s = t; s < np; s += THREADS) {
+      const int q1 = div_small(s, n2, rn2), i2 = s - q1 * n2, i0 = div_small(q1, n1, rn1), i1 = q1 - i0 * n1;
+      auto diff = [&](int i, int m, int st) {    // phi(+1) - phi(-1) along one axis
+        const int c = (i0 * g1 + i1) * p2 + i2;
+        return a[c + (i + 1 == m ? 1 - m : 1) * st].x * scale - a[c + (i == 0 ? m - 1 : -1) * st].x * scale;
+      };
+      q.accel[s] = -diff(i0, g0, g1 * p2) * q.h[0];
+      q.accel[np + s] = -diff(i1, g1, p2) * q.h[1];
+      q.accel[2 * np + s] = -diff(i2, g2, 1) * q.h[2];
+    }
+  }
+  if (q.phi) {
+    const int e1 = n1 + 2, e2 = n2 + 2, ext = (n0 + 2) * e1 * e2;
+    const float re2 = 1.0f / (float)e2, re1 = 1.0f / (float)e1;
+    auto wrap = [](int i, int m) { return i < 0 ? i + m : (i >= m ? i - m : i); };
+#pragma unroll 1
+    for (int s = t; s < ext; s += THREADS) {
+      const int q1 = div_small(s, e2, re2), i2 = s - q1 * e2, i0 = div_small(q1, e1, re1), i1 = q1 - i0 * e1;
+      q.phi[s] = a[(wrap(i0 - 1, g0) * g1 + wrap(i1 - 1, g1)) * p2 + wrap(i2 - 1, g2)].x * scale;
+    }
+  }
+}
+
 __global__ void load_rho_kernel(double2* data, Grid3 g, const double* rho, Grid3 n)
 {
   const long long tot = (long long)g.m[0] * g.m[1] * g.m[2];
@@ -289,8 +568,9 @@ __global__ void load_rho_kernel(double2* data, Grid3 g, const double* rho, Grid3
 }
 
 // G_hat(k) = -pi G / sum_l sin^2(pi k_l / M_l) / d_l^2 (Eq. (20), unequal
-// spacings), zero at k = 0.
-__global__ void green_periodic_kernel(double2* data, Grid3 g, double G, double d0, double d1, double d2)
+// spacings), zero at k = 0, from the axes' tables of sin^2(pi k / M) / d^2.
+__global__ void green_periodic_kernel(double2* data, Grid3 g, double G, const double* s0, const double* s1,
+                                      const double* s2)
 {
   const long long tot = (long long)g.m[0] * g.m[1] * g.m[2];
   const double pi = 3.14159265358979323846;
@@ -299,11 +579,8 @@ __global__ void green_periodic_kernel(double2* data, Grid3 g, double G, double d
     const int k2 = (int)(s % g.m[2]);
     const int k1 = (int)((s / g.m[2]) % g.m[1]);
     const int k0 = (int)(s / ((long long)g.m[2] * g.m[1]));
-    const double s0 = sinpi((double)k0 / g.m[0]);
-    const double s1 = sinpi((double)k1 / g.m[1]);
-    const double s2 = sinpi((double)k2 / g.m[2]);
-    const double den = s0 * s0 / (d0 * d0) + s1 * s1 / (d1 * d1) + s2 * s2 / (d2 * d2);
-    const double gk = (k0 == 0 && k1 == 0 && k2 == 0) ? 0.0 : -pi * G / den;
+    const double den = s0[k0] + s1[k1] + s2[k2];
+    const double gk = s == 0 ? 0.0 : -pi * G / den;
     const double2 v = data[s];
     data[s] = make_double2(v.x * gk, v.y * gk);
   }
@@ -816,9 +1093,9 @@ hipError_t launch_density_from_parts(double* rho, const double* part, long long 
   return hipGetLastError();
 }
 
-hipError_t launch_twiddles(double2* w, int M, hipStream_t s)
+hipError_t launch_twiddles(double2* w, double* s2, int M, double d, hipStream_t s)
 {
-  hipLaunchKernelGGL(twiddle_kernel, dim3((M + 127) / 128), dim3(128), 0, s, w, M);
+  hipLaunchKernelGGL(twiddle_kernel, dim3((M + 127) / 128), dim3(128), 0, s, w, s2, M, d);
   return hipGetLastError();
 }
 
@@ -865,6 +1142,96 @@ hipError_t launch_dft_axis(double2* data, Grid3 g, int axis, int sign, const dou
   return hipGetLastError();
 }
 
+// Transform grids of up to 640 or 4608 cells, rows padded (2 x 72 KiB of LDS), and axes whose
+// twiddles fit the table take the one-workgroup solve. Longer grids would leave
+// the rest of the chip idle for longer than the separate launches cost.
+bool gravity_small_supported(Grid3 g)
+{
+  return (long long)g.m[0] * g.m[1] * (g.m[2] | 1) <= 4608 && g.m[0] <= 128 && g.m[1] <= 128 && g.m[2] <= 128;
+}
+
+// workgroup size: four waves for 512 cells (a line of eight cells is a lane's
+// work, so that 64 lanes transform), eight beyond
+static int gravity_small_threads(Grid3 g) { return (long long)g.m[0] * g.m[1] * (g.m[2] | 1) <= 640 ? 256 : 512; }
+
+// the stages of the three axes (whole lines of up to 16 cells; else fours, then
+// a two, then threes) and the reciprocals that the kernel divides by
+void gravity_small_plan(SmallGravity& q)
+{
+  const int g1 = q.g.m[1], g2 = q.g.m[2], p2 = g2 | 1, tot = q.g.m[0] * g1 * g2;
+  int woff = 0;
+  q.scale = 1.0 / (double)tot;
+  q.nstage = 0;
+  for (int ax = 0; ax < 3; ax++) {
+    const int M = q.g.m[ax];
+    SgStage c{};
+    // stride along the line, lines side by side (cols, in rows of `row` cells
+    // with `pad` unused places after each), stride between their groups
+    c.inner = ax == 0 ? g1 * p2 : (ax == 1 ? p2 : 1);
+    c.cols = ax == 0 ? g1 * g2 : (ax == 1 ? g2 : 1);
+    c.row = g2;
+    c.pad = p2 - g2;
+    c.outer = ax == 0 ? 0 : (ax == 1 ? g1 * p2 : p2);
+    c.woff = woff;
+    c.r_cols = 1.0f / (float)c.cols;
+    c.r_row = 1.0f / (float)c.row;
+    if (M > 1 && M <= 16) {
+      c.R = 100 + M;
+      c.step = tot / M;   // lines
+      q.stage[q.nstage++] = c;
+    }
+    for (int ns = 1; M > 16 && ns < M;) {
+      const int rest = M / ns;
+      c.R = rest % 4 == 0 ? 4 : (rest % 2 == 0 ? 2 : 3);
+      c.ns = ns;
+      c.step = M / c.R;
+      c.tws = c.step / ns;
+      c.r_step = 1.0f / (float)c.step;
+      c.r_ns = 1.0f / (float)ns;
+      q.stage[q.nstage++] = c;
+      ns *= c.R;
+    }
+    woff += M;
+    q.h[ax] = 1.0 / (2.0 * q.d[ax]);
+  }
+  const int np = q.n.m[0] * q.n.m[1] * q.n.m[2], th = gravity_small_threads(q.g);
+  q.groups = np >= th ? 1 : th / np;
+  q.rg2 = 1.0f / (float)q.g.m[2];
+  q.rg1 = 1.0f / (float)q.g.m[1];
+  q.rn2 = 1.0f / (float)q.n.m[2];
+  q.rn1 = 1.0f / (float)q.n.m[1];
+}
+
+hipError_t launch_gravity_small(const SmallGravity& q, hipStream_t s)
+{
+  if (!gravity_small_supported(q.g) || q.nstage > SG_STAGES) return hipErrorInvalidValue;
+  if (gravity_small_threads(q.g) == 256) {
+    if (q.lam_a)
+      hipLaunchKernelGGL((gravity_small_kernel<640, 256, true>), dim3(1), dim3(256), 0, s, q);
+    else
+      hipLaunchKernelGGL((gravity_small_kernel<640, 256, false>), dim3(1), dim3(256), 0, s, q);
+  } else if (q.lam_a) {
+    hipLaunchKernelGGL((gravity_small_kernel<4608, 512, true>), dim3(1), dim3(512), 0, s, q);
+  } else {
+    hipLaunchKernelGGL((gravity_small_kernel<4608, 512, false>), dim3(1), dim3(512), 0, s, q);
+  }
+  return hipGetLastError();
+}
+
+// data = 1: load for the Green's function of a periodic grid as a spectrum
+__global__ void ones_kernel(double2* data, long long tot)
+{
+  for (long long s = blockIdx.x * (long long)blockDim.x + threadIdx.x; s < tot; s += (long long)gridDim.x * blockDim.x)
+    data[s] = make_double2(1.0, 0.0);
+}
+
+hipError_t launch_green_table(double2* data, Grid3 g, double G, const double* const s2[3], hipStream_t s)
+{
+  const long long tot = (long long)g.m[0] * g.m[1] * g.m[2];
+  hipLaunchKernelGGL(ones_kernel, dim3(grid_for(tot, 256)), dim3(256), 0, s, data, tot);
+  return launch_green_periodic(data, g, G, s2, s);
+}
+
 hipError_t launch_load_rho(double2* data, Grid3 g, const double* rho, Grid3 n, hipStream_t s)
 {
   const long long tot = (long long)g.m[0] * g.m[1] * g.m[2];
@@ -872,10 +1239,11 @@ hipError_t launch_load_rho(double2* data, Grid3 g, const double* rho, Grid3 n, h
   return hipGetLastError();
 }
 
-hipError_t launch_green_periodic(double2* data, Grid3 g, double G, double d0, double d1, double d2, hipStream_t s)
+hipError_t launch_green_periodic(double2* data, Grid3 g, double G, const double* const s2[3], hipStream_t s)
 {
   const long long tot = (long long)g.m[0] * g.m[1] * g.m[2];
-  hipLaunchKernelGGL(green_periodic_kernel, dim3(grid_for(tot, 256)), dim3(256), 0, s, data, g, G, d0, d1, d2);
+  hipLaunchKernelGGL(green_periodic_kernel, dim3(grid_for(tot, 256)), dim3(256), 0, s, data, g, G, s2[0], s2[1],
+                     s2[2]);
   return hipGetLastError();
 }
 

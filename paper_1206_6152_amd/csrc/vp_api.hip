@@ -60,8 +60,9 @@ struct vp_ctx {
   double* phi = nullptr;      // (N+2)^3
   double* accel = nullptr;    // [3][np]
   double2* work = nullptr;    // wg cells
-  double2* kspec = nullptr;   // isolated Green's function spectrum
+  double2* kspec = nullptr;   // Green's function spectrum (isolated, or a small grid)
   double2* tw[3] = {nullptr, nullptr, nullptr};
+  double* s2[3] = {nullptr, nullptr, nullptr};   // sin^2(pi k / M) / dx^2 per axis
   double* part = nullptr;     // 2 * np
   double* red = nullptr;      // vp::RED_DOUBLES doubles on the device: results, then partials
   double* host = nullptr;     // 8 pinned doubles
@@ -73,6 +74,7 @@ struct vp_ctx {
   // workgroup sums of the x sweep (density without another pass over f);
   // null when the x sweep of this grid cannot produce them
   double* xsum = nullptr;
+  vp::SmallGravity sg{};      // the parts of a one-launch gravity solve that do not change
   // per-velocity-cell line coefficients of the one-pass T_z T_y (null when
   // the grid has no such pass)
   void* dtab = nullptr;
@@ -229,6 +231,7 @@ void release(vp_ctx* c)
   hipFree(c->work);
   hipFree(c->kspec);
   for (auto& t : c->tw) hipFree(t);
+  for (auto& t : c->s2) hipFree(t);
   hipFree(c->part);
   hipFree(c->xsum);
   hipFree(c->dtab);
@@ -311,13 +314,20 @@ int drain_events(vp_ctx* c)
 // potential (with ghosts) of the density held in rho_in
 int poisson_from(vp_ctx* c, const double* rho_in, double* phi_out)
 {
+  if (vp::gravity_small_supported(c->wg)) {
+    vp::SmallGravity q = c->sg;
+    q.rho = rho_in;
+    q.phi = phi_out;
+    LAUNCH(c, vp::launch_gravity_small(q, c->stream));
+    return VP_OK;
+  }
   const bool iso = c->cfg.bc == VP_BC_ISOLATED;
   LAUNCH(c, vp::launch_load_rho(c->work, c->wg, rho_in, c->ng, c->stream));
   for (int ax = 0; ax < 3; ax++) LAUNCH(c, vp::launch_dft_axis(c->work, c->wg, ax, -1, c->tw[ax], c->stream));
   if (iso)
     LAUNCH(c, vp::launch_mul_spectrum(c->work, c->kspec, prod3(c->wg.m), c->stream));
   else
-    LAUNCH(c, vp::launch_green_periodic(c->work, c->wg, c->cfg.G, c->dx[0], c->dx[1], c->dx[2], c->stream));
+    LAUNCH(c, vp::launch_green_periodic(c->work, c->wg, c->cfg.G, c->s2, c->stream));
   for (int ax = 0; ax < 3; ax++) LAUNCH(c, vp::launch_dft_axis(c->work, c->wg, ax, +1, c->tw[ax], c->stream));
   LAUNCH(c, vp::launch_extract_phi(phi_out, c->ng, c->work, c->wg, 1.0 / (double)prod3(c->wg.m), c->stream));
   return VP_OK;
@@ -331,22 +341,28 @@ int potential_into(vp_ctx* c, double* phi_out)
   return poisson_from(c, c->rho, phi_out);
 }
 
-int compute_accel(vp_ctx* c)
+// acceleration of the density held in c->rho
+int accel_from_rho(vp_ctx* c)
 {
-  PhaseScope scope(c, 6);
-  int r = potential_into(c, c->phi);
+  if (vp::gravity_small_supported(c->wg)) {
+    vp::SmallGravity q = c->sg;
+    q.rho = c->rho;
+    q.accel = c->accel;
+    LAUNCH(c, vp::launch_gravity_small(q, c->stream));
+    return VP_OK;
+  }
+  int r = poisson_from(c, c->rho, c->phi);
   if (r != VP_OK) return r;
   LAUNCH(c, vp::launch_gradient(c->accel, c->phi, c->ng, c->dx[0], c->dx[1], c->dx[2], c->stream));
   return VP_OK;
 }
 
-// acceleration of the density held in c->rho
-int accel_from_rho(vp_ctx* c)
+int compute_accel(vp_ctx* c)
 {
-  int r = poisson_from(c, c->rho, c->phi);
-  if (r != VP_OK) return r;
-  LAUNCH(c, vp::launch_gradient(c->accel, c->phi, c->ng, c->dx[0], c->dx[1], c->dx[2], c->stream));
-  return VP_OK;
+  PhaseScope scope(c, 6);
+  LAUNCH(c, vp::launch_density(c->f, c->cfg.dtype, c->rho, c->np, c->nv3,
+                               c->dv[0] * c->dv[1] * c->dv[2], c->stream));
+  return accel_from_rho(c);
 }
 
 vp::SweepArgs sweep_args(vp_ctx* c, int axis, double tau)
@@ -474,9 +490,17 @@ int density_adjoint(vp_ctx* c, const double* lam_a)
 {
   const long long ext = (long long)(c->cfg.n[0] + 2) * (c->cfg.n[1] + 2) * (c->cfg.n[2] + 2);
   int r;
-  if (!c->lphi && (r = dalloc(&c->lphi, sizeof(double) * ext, "potential adjoint"))) return r;
+  const bool small = vp::gravity_small_supported(c->wg);
+  if (!small && !c->lphi && (r = dalloc(&c->lphi, sizeof(double) * ext, "potential adjoint"))) return r;
   if (!c->radj && (r = dalloc(&c->radj, sizeof(double) * c->np, "density adjoint"))) return r;
   PhaseScope scope(c, 11);
+  if (small) {
+    vp::SmallGravity q = c->sg;
+    q.lam_a = lam_a;
+    q.radj = c->radj;
+    LAUNCH(c, vp::launch_gravity_small(q, c->stream));
+    return VP_OK;
+  }
   LAUNCH(c, vp::launch_gradient_adj(c->lphi, lam_a, c->ng, c->dx[0], c->dx[1], c->dx[2], c->stream));
   if (c->cfg.bc == VP_BC_ISOLATED) {
     LAUNCH(c, vp::launch_load_ext(c->work, c->wg, c->lphi, c->ng, c->stream));
@@ -488,7 +512,7 @@ int density_adjoint(vp_ctx* c, const double* lam_a)
     LAUNCH(c, vp::launch_fold_periodic(c->radj, c->lphi, c->ng, c->stream));
     LAUNCH(c, vp::launch_load_rho(c->work, c->wg, c->radj, c->ng, c->stream));
     for (int ax = 0; ax < 3; ax++) LAUNCH(c, vp::launch_dft_axis(c->work, c->wg, ax, -1, c->tw[ax], c->stream));
-    LAUNCH(c, vp::launch_green_periodic(c->work, c->wg, c->cfg.G, c->dx[0], c->dx[1], c->dx[2], c->stream));
+    LAUNCH(c, vp::launch_green_periodic(c->work, c->wg, c->cfg.G, c->s2, c->stream));
     for (int ax = 0; ax < 3; ax++) LAUNCH(c, vp::launch_dft_axis(c->work, c->wg, ax, +1, c->tw[ax], c->stream));
     LAUNCH(c, vp::launch_extract_interior(c->radj, c->work, c->wg, c->ng, 1.0 / (double)prod3(c->wg.m), c->stream));
   }
@@ -712,12 +736,14 @@ int vp_init(const vp_config* cfg, void* f_dev, void* hip_stream, vp_ctx** out)
     return r;
   }
   for (int ax = 0; ax < 3; ax++) {
-    if ((r = dalloc(&c->tw[ax], sizeof(double2) * c->wg.m[ax], "twiddles"))) {
+    if ((r = dalloc(&c->tw[ax], sizeof(double2) * c->wg.m[ax], "twiddles")) ||
+        (r = dalloc(&c->s2[ax], sizeof(double) * c->wg.m[ax], "Green's function"))) {
       release(c);
       return r;
     }
   }
-  if (cfg->bc == VP_BC_ISOLATED && (r = dalloc(&c->kspec, sizeof(double2) * wn, "green spectrum"))) {
+  const bool small = vp::gravity_small_supported(c->wg);
+  if ((small || cfg->bc == VP_BC_ISOLATED) && (r = dalloc(&c->kspec, sizeof(double2) * wn, "green spectrum"))) {
     release(c);
     return r;
   }
@@ -749,7 +775,26 @@ int vp_init(const vp_config* cfg, void* f_dev, void* hip_stream, vp_ctx** out)
     return fail(VP_ENOMEM, "hipHostMalloc: %s", hipGetErrorString(he));
   }
   for (int ax = 0; ax < 3; ax++) {
-    if ((r = check_launch(c, vp::launch_twiddles(c->tw[ax], c->wg.m[ax], c->stream), "twiddles"))) {
+    if ((r = check_launch(c, vp::launch_twiddles(c->tw[ax], c->s2[ax], c->wg.m[ax], c->dx[ax], c->stream), "twiddles"))) {
+      release(c);
+      return r;
+    }
+  }
+  if (small) {
+    vp::SmallGravity& q = c->sg;
+    q.n = c->ng;
+    q.g = c->wg;
+    q.isolated = cfg->bc == VP_BC_ISOLATED;
+    q.G = cfg->G;
+    for (int l = 0; l < 3; l++) {
+      q.d[l] = c->dx[l];
+      q.tw[l] = c->tw[l];
+    }
+    q.kspec = c->kspec;
+    q.dv3 = c->dv[0] * c->dv[1] * c->dv[2];
+    vp::gravity_small_plan(q);
+    if (cfg->bc == VP_BC_PERIODIC &&
+        (r = check_launch(c, vp::launch_green_table(c->kspec, c->wg, cfg->G, c->s2, c->stream), "green"))) {
       release(c);
       return r;
     }

@@ -134,20 +134,58 @@ struct Grid3 {
   int m[3];
 };
 
-// Twiddle table w[k] = exp(-2 pi i k / M), k = 0..M-1, as (cos, sin) pairs.
-hipError_t launch_twiddles(double2* w, int M, hipStream_t s);
+// Twiddle table w[k] = exp(-2 pi i k / M), k = 0..M-1, as (cos, sin) pairs, and
+// s2[k] = sin^2(pi k / M) / d^2.
+hipError_t launch_twiddles(double2* w, double* s2, int M, double d, hipStream_t s);
 
 // In-place DFT along one axis of a complex field of shape g (C order);
 // sign -1 forward, +1 inverse (no scaling). tw is the table for g.m[axis].
 hipError_t launch_dft_axis(double2* data, Grid3 g, int axis, int sign, const double2* tw,
                            hipStream_t s);
 
+// The whole gravity solve of a small grid (gravity_small_supported for its
+// transform grid) in one launch. Forward (lam_a null): from rho, or from part
+// (nchunk partial sums per spatial cell, part[k np + cell], times dv3), to the
+// acceleration and/or the ghost-padded potential, whichever is not null.
+// Reverse (lam_a set): radj = G^T D^T lam_a.
+constexpr int SG_STAGES = 16;   // an axis of 128 cells has four stages, one of 96 or 64 three or four
+struct SgStage {       // R > 100: whole lines of R - 100 cells, `step` of them
+  int R, inner, cols, row, pad, outer, ns, step, tws, woff;
+  float r_cols, r_row, r_step, r_ns;
+};
+struct SmallGravity {
+  Grid3 n, g;          // spatial grid, transform grid
+  int isolated;
+  double G, d[3];
+  const double2* tw[3];
+  const double2* kspec;   // Green's function's spectrum
+  const double* rho;
+  const double* part;
+  long long nchunk;
+  double dv3;
+  double* accel;
+  double* phi;
+  const double* lam_a;
+  double* radj;
+  // set by gravity_small_plan from n, g and d
+  int nstage, groups;
+  SgStage stage[SG_STAGES];
+  float rg1, rg2, rn1, rn2;
+  double scale, h[3];
+};
+bool gravity_small_supported(Grid3 g);
+void gravity_small_plan(SmallGravity& q);
+hipError_t launch_gravity_small(const SmallGravity& q, hipStream_t s);
+
 // data = rho (imag 0) on an n-grid (periodic) or zero-padded into the 2n-grid.
 hipError_t launch_load_rho(double2* data, Grid3 g, const double* rho, Grid3 n, hipStream_t s);
 
 // data *= G_hat(k) of the periodic discrete Green's function; zero mode -> 0.
-hipError_t launch_green_periodic(double2* data, Grid3 g, double G, double d0, double d1,
-                                 double d2, hipStream_t s);
+hipError_t launch_green_periodic(double2* data, Grid3 g, double G, const double* const s2[3],
+                                 hipStream_t s);
+
+// data = G_hat(k), as a spectrum
+hipError_t launch_green_table(double2* data, Grid3 g, double G, const double* const s2[3], hipStream_t s);
 
 // data *= spec (complex, same grid)
 hipError_t launch_mul_spectrum(double2* data, const double2* spec, long long count, hipStream_t s);
