@@ -74,7 +74,11 @@ struct vp_ctx {
   // workgroup sums of the x sweep (density without another pass over f);
   // null when the x sweep of this grid cannot produce them
   double* xsum = nullptr;
+  // velocity cells per workgroup of the one-pass drift over all three axes (0:
+  // none for this grid), and its sums, one per chunk and spatial cell
+  int box3 = 0;
   vp::SmallGravity sg{};      // the parts of a one-launch gravity solve that do not change
+  double* bsum = nullptr;
   // per-velocity-cell line coefficients of the one-pass T_z T_y (null when
   // the grid has no such pass)
   void* dtab = nullptr;
@@ -234,6 +238,7 @@ void release(vp_ctx* c)
   for (auto& t : c->s2) hipFree(t);
   hipFree(c->part);
   hipFree(c->xsum);
+  hipFree(c->bsum);
   hipFree(c->dtab);
   hipFree(c->ktab);
   hipFree(c->red);
@@ -530,50 +535,56 @@ int accel_adjoint(vp_ctx* c, const double* lam_a, void* lam)
   return VP_OK;
 }
 
+vp::KickArgs kick_args(vp_ctx* c, double tau, int reps, const void* src, void* dst)
+{
+  vp::KickArgs a{};
+  a.tab = c->ktab;
+  a.f = const_cast<void*>(src);
+  a.out = dst;
+  a.np = c->np;
+  a.reps = reps;
+  for (int l = 0; l < 3; l++) {
+    a.a[l] = c->accel + (long long)l * c->np;
+    a.scale[l] = tau / c->dv[l];
+  }
+  return a;
+}
+
+// True when the velocity block of a spatial cell has a one-pass half kick: in
+// LDS (cubes with a kernel of their own, and any other shape that fits) or,
+// for FP64 32^3, in registers with one line per lane.
+bool kick_one_pass(vp_ctx* c)
+{
+  const int* nv = c->cfg.nv;
+  return vp::kick_fused_supported(c->cfg.dtype, nv) || vp::kick_lines_supported(c->cfg.dtype, nv) ||
+         vp::kick_box_supported(c->cfg.dtype, nv);
+}
+
+// reps (1 or 2) half kicks in one pass, from src (over it, or to dst)
+int kick_pass(vp_ctx* c, double tau, int reps, const void* src, void* dst)
+{
+  const int* nv = c->cfg.nv;
+  const int dt = c->cfg.dtype;
+  const vp::KickArgs a = kick_args(c, tau, reps, src, dst);
+  PhaseScope scope(c, reps == 2 ? 8 : 7);
+  if (vp::kick_fused_supported(dt, nv))
+    LAUNCH(c, vp::launch_kick(a, dt, nv, c->stream));
+  else if (vp::kick_lines_supported(dt, nv))
+    LAUNCH(c, vp::launch_kick_lines(a, dt, nv, c->stream));
+  else
+    LAUNCH(c, vp::launch_kick_box(a, dt, nv, c->stream));
+  return VP_OK;
+}
+
 // T_vz T_vy T_vx(tau), reps times in a row with the same acceleration: one
 // pass over f when the velocity block fits on chip.
 int kick_n(vp_ctx* c, double tau, int reps)
 {
+  if (kick_one_pass(c)) return kick_pass(c, tau, reps, c->f, nullptr);
   const int nv[3] = {c->cfg.nv[0], c->cfg.nv[1], c->cfg.nv[2]};
-  if (vp::kick_fused_supported(c->cfg.dtype, nv)) {
-    vp::KickArgs a{};
-    a.tab = c->ktab;
-    a.f = c->f;
-    a.np = c->np;
-    a.reps = reps;
-    for (int l = 0; l < 3; l++) {
-      a.a[l] = c->accel + (long long)l * c->np;
-      a.scale[l] = tau / c->dv[l];
-    }
-    PhaseScope scope(c, reps == 2 ? 8 : 7);
-    LAUNCH(c, vp::launch_kick(a, c->cfg.dtype, nv, c->stream));
-    return VP_OK;
-  }
-  if (vp::kick_lines_supported(c->cfg.dtype, nv)) {   // FP64 32^3: one line per lane, LDS between axes
-    vp::KickArgs a{};
-    a.tab = c->ktab;
-    a.f = c->f;
-    a.np = c->np;
-    a.reps = reps;
-    for (int l = 0; l < 3; l++) {
-      a.a[l] = c->accel + (long long)l * c->np;
-      a.scale[l] = tau / c->dv[l];
-    }
-    PhaseScope scope(c, reps == 2 ? 8 : 7);
-    LAUNCH(c, vp::launch_kick_lines(a, c->cfg.dtype, nv, c->stream));
-    return VP_OK;
-  }
   int r;
   if (vp::kick_planes_supported(c->cfg.dtype, nv)) {   // T_vx | T_vy T_vz per half kick
-    vp::KickArgs a{};
-    a.tab = c->ktab;
-    a.f = c->f;
-    a.np = c->np;
-    a.reps = 1;
-    for (int l = 0; l < 3; l++) {
-      a.a[l] = c->accel + (long long)l * c->np;
-      a.scale[l] = tau / c->dv[l];
-    }
+    const vp::KickArgs a = kick_args(c, tau, 1, c->f, nullptr);
     if (reps == 2 && vp::kick_slices_supported(c->cfg.dtype, nv)) {   // T_vx T_vy | T_vz T_vx | T_vy T_vz
       for (int pass = 0; pass < 3; pass++) {
         PhaseScope scope(c, 12);
@@ -595,12 +606,36 @@ int kick_n(vp_ctx* c, double tau, int reps)
 
 int kick(vp_ctx* c, double tau) { return kick_n(c, tau, 1); }
 
-// T_x T_y T_z(tau): z and y in one pass when the (y, z) plane fits on chip;
-// with x_sums the x sweep also writes its workgroup sums to c->xsum
+// T_x T_y T_z(tau) over chunks of velocity cells (box.h); with sums the chunks'
+// density sums go to c->bsum
+int drift_box(vp_ctx* c, double tau, bool sums)
+{
+  const auto& k = c->cfg;
+  vp::DriftBoxArgs a{};
+  a.f = c->f;
+  a.nv3 = c->nv3;
+  a.periodic = (k.bc == VP_BC_PERIODIC) ? 1 : 0;
+  a.part = sums ? c->bsum : nullptr;
+  for (int l = 0; l < 3; l++) {
+    a.n[l] = k.n[l];
+    a.nv[l] = k.nv[l];
+    a.vmin[l] = k.vmin[l];
+    a.dv[l] = c->dv[l];
+    a.scale[l] = tau / c->dx[l];
+  }
+  PhaseScope scope(c, 9);
+  LAUNCH(c, vp::launch_drift_box(a, k.dtype, c->stream));
+  return VP_OK;
+}
+
+// T_x T_y T_z(tau): in one pass when the whole spatial grid fits on chip with a
+// chunk of velocity cells; else z and y in one pass when the (y, z) plane does.
+// With sums the last pass leaves density sums (c->bsum, c->xsum).
 int drift(vp_ctx* c, double tau, bool x_sums = false)
 {
   int r;
   const auto& k = c->cfg;
+  if (c->box3) return drift_box(c, tau, x_sums);
   if (vp::drift_yz_supported(k.dtype, k.n[1], k.n[2], c->nv3, k.nv[2])) {
     vp::DriftArgs a{};
     a.f = c->f;
@@ -638,6 +673,24 @@ int drift(vp_ctx* c, double tau, bool x_sums = false)
 // density pass over f by a reduction of those sums
 int drift_accel(vp_ctx* c, double tau)
 {
+  if (c->box3) {
+    int r = drift(c, tau, /*x_sums=*/true);
+    if (r) return r;
+    PhaseScope scope(c, 6);
+    const long long nchunk = (c->nv3 + c->box3 - 1) / c->box3;
+    // few sums: the one-workgroup solve adds them itself (512 KiB take it about
+    // the time of the launch that it saves)
+    if (vp::gravity_small_supported(c->wg) && c->np * nchunk <= 65536) {
+      vp::SmallGravity q = c->sg;
+      q.part = c->bsum;
+      q.nchunk = nchunk;
+      q.accel = c->accel;
+      LAUNCH(c, vp::launch_gravity_small(q, c->stream));
+      return VP_OK;
+    }
+    LAUNCH(c, vp::launch_box_density(c->rho, c->bsum, c->np, nchunk, c->dv[0] * c->dv[1] * c->dv[2], c->stream));
+    return accel_from_rho(c);
+  }
   if (!c->xsum) {
     int r = drift(c, tau);
     return r ? r : compute_accel(c);
@@ -747,7 +800,14 @@ int vp_init(const vp_config* cfg, void* f_dev, void* hip_stream, vp_ctx** out)
     release(c);
     return r;
   }
-  if (x_sweep_sums(c)) {   // n_x sums per 256 lines of the x sweep
+  c->box3 = vp::drift_box_cells(cfg->dtype, cfg->n, c->nv3);
+  if (c->box3) {
+    const long long nsum = (c->nv3 + c->box3 - 1) / c->box3 * c->np;
+    if ((r = dalloc(&c->bsum, sizeof(double) * nsum, "drift sums"))) {
+      release(c);
+      return r;
+    }
+  } else if (x_sweep_sums(c)) {   // n_x sums per 256 lines of the x sweep
     const long long nsum = (long long)cfg->n[1] * cfg->n[2] * (c->nv3 / 256) * cfg->n[0];
     if ((r = dalloc(&c->xsum, sizeof(double) * nsum, "x sweep sums"))) {
       release(c);
@@ -1079,24 +1139,9 @@ int copy_f(vp_ctx* c, void* dst, const void* src, size_t bytes)
 // copy and the kick in place. c->f is left pointing at dst.
 int kick_to(vp_ctx* c, double tau, const void* src, void* dst, size_t fbytes)
 {
-  const int nv[3] = {c->cfg.nv[0], c->cfg.nv[1], c->cfg.nv[2]};
-  const bool lines = vp::kick_lines_supported(c->cfg.dtype, nv);
-  if (lines || vp::kick_fused_supported(c->cfg.dtype, nv)) {
-    vp::KickArgs a{};
-    a.tab = c->ktab;
-    a.f = const_cast<void*>(src);
-    a.out = dst;
-    a.np = c->np;
-    a.reps = 1;
-    for (int l = 0; l < 3; l++) {
-      a.a[l] = c->accel + (long long)l * c->np;
-      a.scale[l] = tau / c->dv[l];
-    }
+  if (kick_one_pass(c)) {
     c->f = dst;
-    PhaseScope scope(c, 7);
-    LAUNCH(c, lines ? vp::launch_kick_lines(a, c->cfg.dtype, nv, c->stream)
-                    : vp::launch_kick(a, c->cfg.dtype, nv, c->stream));
-    return VP_OK;
+    return kick_pass(c, tau, 1, src, dst);
   }
   int r = copy_f(c, dst, src, fbytes);
   if (r) return r;

@@ -109,6 +109,29 @@ size_t drift_table_bytes(int dtype, long long nv3);
 bool drift_yz_supported(int dtype, int ny, int nz, long long nv3, long long nvz);
 hipError_t launch_drift_yz(const DriftArgs& a, int dtype, hipStream_t s);
 
+// The half kick (or two) of a velocity block of any shape that fits the LDS, in
+// one pass (box.h).
+bool kick_box_supported(int dtype, const int nv[3]);
+hipError_t launch_kick_box(const KickArgs& a, int dtype, const int nv[3], hipStream_t s);
+
+// T_x T_y T_z(tau) in one pass over chunks of drift_box_cells velocity cells of
+// the whole spatial grid (box.h). part, if not null, receives the sum of the new
+// f over each chunk's velocity cells for every spatial cell: part[chunk np + cell].
+struct DriftBoxArgs {
+  const void* f;
+  void* out;      // null: over f
+  int n[3], nv[3];
+  long long nv3;
+  int periodic;
+  double vmin[3], dv[3], scale[3];   // scale = tau / dx
+  double* part;
+};
+int drift_box_cells(int dtype, const int n[3], long long nv3);
+hipError_t launch_drift_box(const DriftBoxArgs& a, int dtype, hipStream_t s);
+// rho[cell] = dv3 sum_k part[k np + cell], k < nchunk, in a fixed order
+hipError_t launch_box_density(double* rho, const double* part, long long np, long long nchunk, double dv3,
+                              hipStream_t s);
+
 // ---- gravity and reductions (FP64) ----------------------------------------
 
 // rho[s] = dv3 * sum_j f[s*nv3 + j]
