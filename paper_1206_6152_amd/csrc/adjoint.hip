@@ -19,7 +19,7 @@
 //   cell holding the maximum, and lam_nu = sign * lam_alpha.
 // A velocity sweep's nu = a_l(x) tau / dv_l sends lam_nu to the acceleration;
 // the per-line values are reduced per spatial cell in a fixed order.
-#include "pfc_line.h"
+#include "adj_line.h"
 #include "vec16.h"
 #include "vp_internal.h"
 
@@ -27,166 +27,61 @@ namespace vp {
 namespace {
 
 // Reverse of pfc_line + store_shifted for one line; returns d<lam_out, out>/d nu.
-// `at(r)` is the offset of storage cell r of the lane's line from both bases.
-//
-// The view runs along the transport direction: view cell i is storage cell i
-// (nu >= 0) or N-1-i (nu < 0); the lane's forward line and lam line are
-// mirrored into the view with selects, so every lane follows the same
-// instruction stream whatever its sign. In the view the shift is
-// m = floor(|nu|) >= 0 and its transpose is lam_g_k = lam_out_{k+m} (zero
-// beyond an outflow end, wrapped if periodic). One pass over the cells in view
-// order then writes out_{i-1} once cell i is known: cell i sends its own terms
-// to out_i, its Lp interior-branch term to out_{i+1} and its Lm interior-branch
-// term to out_{i-1}.
-// la(r, x) gives the lam value of cell r from its stored value x.
-// GATHER (lines in LDS): where the line has a whole-cell shift, lam_g is
-// read straight into view order, each view cell from the storage cell that
-// the mirror and the transposed shift name, instead of loading lam in
-// storage order and permuting registers with selects (N^2 of them for the
-// shift); the same values land in the same registers.
-template <typename T, int N, bool GATHER = false, typename AT, typename LA>
+// `at(r)` is the offset of storage cell r of the lane's line from both bases,
+// la(r, x) the lam value of cell r from its stored value x. The view runs along
+// the transport direction: view cell i is storage cell i (nu >= 0) or N-1-i
+// (nu < 0). The lane's forward line is mirrored into the view with selects, so
+// every lane follows the same instruction stream whatever its sign. In the
+// view the shift's transpose is lam_g_k = lam_out_{k+m} (zero beyond an outflow
+// end, wrapped if periodic): where the line has a whole-cell shift, lam_g is
+// read straight into view order, each view cell from the storage cell that the
+// mirror and the transposed shift name.
+template <typename T, int N, typename AT, typename LA>
 __device__ __forceinline__ double adj_line(const T* fin, T* lam, double nu, bool periodic, AT at, LA la)
 {
-#pragma clang fp contract(off)
-  const LineCoef<T> k = line_coef<T, N>(nu, periodic);
+  const AdjCoef<T> k = adj_coef<T, N>(nu, periodic);
   const bool neg = k.neg;
   T w[N], l[N];
-  if constexpr (GATHER) {
-    const int m = neg ? -k.shift : k.shift;   // >= 0, below N when periodic
 #pragma unroll
-    for (int r = 0; r < N; r++) w[r] = fin[at(r)];
-    if (m == 0) {                             // no shift: storage order, then the mirror
+  for (int r = 0; r < N; r++) w[r] = fin[at(r)];
+  if (k.shift == 0) {                         // storage order, then the mirror
 #pragma unroll
-      for (int r = 0; r < N; r++) l[r] = la(r, lam[at(r)]);
+    for (int r = 0; r < N; r++) l[r] = la(r, lam[at(r)]);
 #pragma unroll
-      for (int i = 0; i < N / 2; i++) {
-        const T p = l[i], q = l[N - 1 - i];
-        l[i] = neg ? q : p;
-        l[N - 1 - i] = neg ? p : q;
-      }
-    } else {
-#pragma unroll
-      for (int i = 0; i < N; i++) {
-        int j = i + m;
-        if (periodic && j >= N) j -= N;
-        const bool in = j < N;                // else past an outflow end: zero
-        const int rs = in ? (neg ? N - 1 - j : j) : 0;
-        const T x = la(rs, lam[at(rs)]);
-        l[i] = in ? x : T(0);
-      }
+    for (int i = 0; i < N / 2; i++) {
+      const T p = l[i], q = l[N - 1 - i];
+      l[i] = neg ? q : p;
+      l[N - 1 - i] = neg ? p : q;
     }
   } else {
+    int m = k.shift;
+    asm volatile("" : "+v"(m));               // the places below stay inside this rarely taken branch
 #pragma unroll
-    for (int r = 0; r < N; r++) {
-      w[r] = fin[at(r)];
-      l[r] = la(r, lam[at(r)]);
+    for (int i = 0; i < N; i++) {
+      int j = i + m;
+      if (periodic && j >= N) j -= N;
+      const bool in = j < N;                  // else past an outflow end: zero
+      const int rs = in ? (neg ? N - 1 - j : j) : 0;
+      const T x = la(rs, lam[at(rs)]);
+      l[i] = in ? x : T(0);
     }
   }
-  // f_inf and the first storage cell that holds it
+  // f_inf and the first storage cell that holds it (none on an empty line)
   T finf = T(0);
+#pragma unroll
+  for (int r = 0; r < N; r++) finf = max_(finf, w[r]);
   int am = -1;
 #pragma unroll
-  for (int r = 0; r < N; r++)
-    if (w[r] > finf) {
-      finf = w[r];
-      am = r;
-    }
-  const int amv = (neg && am >= 0) ? N - 1 - am : am;   // its view index
+  for (int r = N - 1; r >= 0; r--) am = w[r] == finf ? r : am;
+  if (!(finf > T(0))) am = -1;
 #pragma unroll
   for (int i = 0; i < N / 2; i++) {
     const T x = w[i], y = w[N - 1 - i];
     w[i] = neg ? y : x;
     w[N - 1 - i] = neg ? x : y;
-    if constexpr (!GATHER) {
-      const T p = l[i], q = l[N - 1 - i];
-      l[i] = neg ? q : p;
-      l[N - 1 - i] = neg ? p : q;
-    }
   }
-  const int m = neg ? -k.shift : k.shift;
-  if (!GATHER && m != 0) {
-    T g[N];
-#pragma unroll
-    for (int i = 0; i < N; i++) {
-      int src = i + m;
-      if (periodic) src %= N;
-      T x = T(0);
-#pragma unroll
-      for (int j = 0; j < N; j++)
-        if (j == src) x = l[j];
-      g[i] = x;
-    }
-#pragma unroll
-    for (int i = 0; i < N; i++) l[i] = g[i];
-  }
-  const double a = fabs(nu);
-  const double al = a - floor(a);
-  const T dc1 = (T)((2.0 * al - 3.0) / 6.0);
-  const T dc2 = (T)(-al / 3.0);
-  const T alpha = k.alpha, c1 = k.c1, c2 = k.c2;
-  const T twoinf = finf + finf;
-  const T lg0 = l[0];
-  T dm = periodic ? w[0] - w[N - 1] : w[0];
-  // d<lam_out, out>/d alpha = sum_i lam_F_i d F_i / d alpha, first on its own
-  T lalpha = T(0);
-  {
-    T dmq = periodic ? w[0] - w[N - 1] : w[0];
-#pragma unroll
-    for (int i = 0; i < N; i++) {
-      const T f0 = w[i];
-      const T fr = (i + 1 < N) ? w[i + 1 < N ? i + 1 : 0] : (periodic ? w[0] : T(0));
-      const T dp = fr - f0;
-      const T h = f0 + f0;
-      const T r = twoinf - h;
-      const T lp = clamp_ordered(dp, -r, h);
-      const T lm = clamp_ordered(dmq, -h, r);
-      const T lgn = (i + 1 < N) ? l[i + 1 < N ? i + 1 : 0] : (periodic ? lg0 : T(0));
-      const T lF = lgn - l[i];
-      const T q = fma_(c2, lm, fma_(c1, lp, f0));
-      lalpha = lalpha + lF * (q + alpha * (dc1 * lp + dc2 * lm));
-      dmq = dp;
-    }
-  }
-  // fresh copies, so that nothing of the first pass is kept for the second
-#pragma unroll
-  for (int i = 0; i < N; i++) asm volatile("" : "+v"(w[i]));
-  T lfinf = T(0);
-  T carry = T(0), pending = T(0), wrap_back = T(0);
-#pragma unroll
-  for (int i = 0; i < N; i++) {
-    const T f0 = w[i];
-    const T fr = (i + 1 < N) ? w[i + 1 < N ? i + 1 : 0] : (periodic ? w[0] : T(0));
-    const T dp = fr - f0;
-    const T h = f0 + f0;
-    const T r = twoinf - h;
-    const T lgi = l[i];
-    const T lgn = (i + 1 < N) ? l[i + 1 < N ? i + 1 : 0] : (periodic ? lg0 : T(0));
-    const T lF = lgn - lgi;                      // lam_F_i = lam_g_{i+1} - lam_g_i
-    const T lin = alpha * lF;
-    const T llp = c1 * lin;
-    const T llm = c2 * lin;
-    const bool p_lo = dp < -r, p_hi = dp > h;
-    const bool m_lo = dm < -h, m_hi = dm > r;
-    const bool p_mid = !(p_lo || p_hi), m_mid = !(m_lo || m_hi);
-    T own = lgi + lin;
-    own = own + (p_mid ? -llp : T(2) * llp);
-    own = own + (m_mid ? llm : -(T(2) * llm));
-    own = own + carry;
-    lfinf = lfinf - (p_lo ? T(2) * llp : T(0));
-    lfinf = lfinf + (m_hi ? T(2) * llm : T(0));
-    const T back = m_mid ? -llm : T(0);
-    if (i > 0) l[i > 0 ? i - 1 : 0] = pending + back;
-    else wrap_back = back;
-    pending = own;
-    carry = p_mid ? llp : T(0);
-    dm = dp;
-  }
-  l[N - 1] = pending + (periodic ? wrap_back : T(0));
-  if (periodic) l[0] = l[0] + carry;
-#pragma unroll
-  for (int i = 0; i < N; i++) {
-    if (i == amv) l[i] = l[i] + lfinf;
-  }
+  T lfinf, lalpha;
+  adj_core<T, N>(w, l, finf, k, periodic, lfinf, lalpha);
   // back to storage order
 #pragma unroll
   for (int i = 0; i < N / 2; i++) {
@@ -195,14 +90,14 @@ __device__ __forceinline__ double adj_line(const T* fin, T* lam, double nu, bool
     l[N - 1 - i] = neg ? p : q;
   }
 #pragma unroll
-  for (int r = 0; r < N; r++) lam[at(r)] = l[r];
+  for (int r = 0; r < N; r++) lam[at(r)] = r == am ? l[r] + lfinf : l[r];
   return neg ? -(double)lalpha : (double)lalpha;
 }
 
-template <typename T, int N, bool GATHER = false, typename AT>
+template <typename T, int N, typename AT>
 __device__ __forceinline__ double adj_line(const T* fin, T* lam, double nu, bool periodic, AT at)
 {
-  return adj_line<T, N, GATHER>(fin, lam, nu, periodic, at, [](int, T x) { return x; });
+  return adj_line<T, N>(fin, lam, nu, periodic, at, [](int, T x) { return x; });
 }
 
 __device__ __forceinline__ double adj_line_nu(const SweepArgs& a, long long o, long long c)
@@ -345,179 +240,6 @@ __global__ __launch_bounds__(256) void reduce_lines_kernel(double* lam_a, const 
   if (threadIdx.x == 0) lam_a[s] += scale * sh[0];
 }
 
-// ---- reverse of one half kick in one pass --------------------------------------
-// The adjoint of T_vz T_vy T_vx (tau) for velocity blocks of which two copies
-// fit the LDS: the block's forward input x and its adjoint lam are staged
-// (16-byte loads, storage order, rows padded to N + 1 and planes to
-// SX = N (mod 64)); the forward states the reverse sweeps need are rebuilt in
-// LDS with the forward line update, and the reverse line updates run in
-// place on lam:
-//   B = T_vy T_vx x;  lam <- vz reverse at B;
-//   B = T_vx x;       lam <- vy reverse at B;
-//   B = x;            lam <- vx reverse at B;
-// then lam goes back to HBM. x crosses HBM up to three times (the reloads
-// mostly hit in L2) and lam twice, against twelve passes for two regenerated
-// states and three separate reverse sweeps. Each reverse line runs adj_line
-// on the same inputs as the single reverse sweep, and the per-line nu
-// adjoints are added per axis in the order of reduce_lines_kernel, so the
-// results are those of the separate passes bit for bit.
-template <typename T, int N>
-struct AdjKickShape {
-  static constexpr int SY = N + 1;
-  static constexpr int SX0 = N * SY;
-  static constexpr int SX = SX0 + ((((N - SX0) % 64) + 64) % 64);
-  static constexpr int ELEMS = N * SX;
-  static constexpr int LINES = N * N;
-  // at least 256 lanes: the reduction below runs the 256-lane tree of reduce_lines_kernel
-  static constexpr int THREADS = (LINES + 63) / 64 * 64 > 256 ? (LINES + 63) / 64 * 64 : 256;
-  static constexpr int BYTES = 2 * ELEMS * (int)sizeof(T) + 3 * LINES * (int)sizeof(double) + 3 * 256 * (int)sizeof(double);
-  static constexpr bool fits = BYTES <= 160 * 1024 && THREADS <= 1024 && N % (16 / (int)sizeof(T)) == 0;
-};
-
-template <typename T, int N>
-__global__ __launch_bounds__((AdjKickShape<T, N>::THREADS)) void kick_adj_block(KickAdjArgs a)
-{
-  using S = AdjKickShape<T, N>;
-  using VT = typename Vec16<T>::type;
-  constexpr int V = Vec16<T>::n;
-  constexpr int NVEC = N * N * N / V;
-  __shared__ T B[S::ELEMS];
-  __shared__ T C[S::ELEMS];
-  __shared__ double dn[3][S::LINES];
-  __shared__ double sh[3][256];
-  const int tid = threadIdx.x;
-  const long long s = blockIdx.x;
-  const T* xg = static_cast<const T*>(a.fin) + s * (long long)(N * N * N);
-  T* lg = static_cast<T*>(a.lam) + s * (long long)(N * N * N);
-  const double nux = a.accel[0][s] * a.scale[0], nuy = a.accel[1][s] * a.scale[1], nuz = a.accel[2][s] * a.scale[2];
-  auto place = [](int e) {   // storage element e -> LDS index
-    const int jz = e % N, jy = (e / N) % N, jx = e / (N * N);
-    return jx * S::SX + jy * S::SY + jz;
-  };
-  // staging: every 16-byte load of a lane is in flight before its first LDS
-  // write (a rolled loop would wait out one load latency per vector); the
-  // opaque copies of the lane index keep the compiler from holding the
-  // addresses of every staging for the whole kernel
-  constexpr int PER = (NVEC + S::THREADS - 1) / S::THREADS;
-  auto load = [&](VT (&x)[PER], const T* src) {
-    int t0 = tid;
-    asm volatile("" : "+v"(t0));
-#pragma unroll
-    for (int j = 0; j < PER; j++) {
-      const int k = t0 + j * S::THREADS;
-      if (k < NVEC) x[j] = reinterpret_cast<const VT*>(src)[k];
-    }
-  };
-  auto park = [&](T* dst, const VT (&x)[PER]) {
-    int t0 = tid;
-    asm volatile("" : "+v"(t0));
-#pragma unroll
-    for (int j = 0; j < PER; j++) {
-      const int k = t0 + j * S::THREADS;
-      if (k < NVEC) {
-        const int b = place(k * V);
-#pragma unroll
-        for (int q = 0; q < V; q++) dst[b + q] = lane_of<VT, T>(x[j], q);
-      }
-    }
-  };
-  auto stage = [&](T* dst, const T* src) {
-    VT x[PER];
-    load(x, src);
-    park(dst, x);
-  };
-  // forward sweep of B along vx (lanes (jy, jz)) or vy (lanes (jx, jz)), in place
-  // the sweep lambdas are inlined at each call, so that their axis, hence
-  // every LDS stride, is a constant there (a shared out-of-line body takes the
-  // strides at run time and spills across the calls)
-  auto forward = [&](int axis, double nu) __attribute__((always_inline)) {
-    if (tid < S::LINES) {
-      const int o = tid / N, i = tid - o * N;
-      const int base = axis == 0 ? o * S::SY + i : o * S::SX + i;
-      const int st = axis == 0 ? S::SX : S::SY;
-      T v[N];
-#pragma unroll
-      for (int r = 0; r < N; r++) v[r] = B[base + r * st];
-      const LineCoef<T> k = pfc_line<T, N>(v, nu, false);
-      store_shifted<T, N>(v, k.shift, false, [&](int r, T x) { B[base + r * st] = x; });
-    }
-    __syncthreads();
-  };
-  // reverse sweep along `axis` at forward input B, lam in C, in place
-  auto reverse = [&](int axis, double nu) __attribute__((always_inline)) {
-    if (tid < S::LINES) {
-      const int o = tid / N, i = tid - o * N;
-      int base, st;
-      if (axis == 2) { base = o * S::SX + i * S::SY; st = 1; }          // vz lines, lanes (jx, jy)
-      else if (axis == 1) { base = o * S::SX + i; st = S::SY; }        // vy lines, lanes (jx, jz)
-      else { base = o * S::SY + i; st = S::SX; }                      // vx lines, lanes (jy, jz)
-      dn[axis][tid] = adj_line<T, N, true>(B, C, nu, false, [&](int r) { return base + r * st; });
-    }
-    __syncthreads();
-  };
-  {
-    VT x[PER], l[PER];
-    load(x, xg);
-    load(l, lg);
-    park(B, x);
-    park(C, l);
-  }
-  __syncthreads();
-  forward(0, nux);
-  forward(1, nuy);
-  reverse(2, nuz);
-  stage(B, xg);
-  __syncthreads();
-  forward(0, nux);
-  reverse(1, nuy);
-  stage(B, xg);
-  __syncthreads();
-  reverse(0, nux);
-#pragma unroll
-  for (int j = 0; j < PER; j++) {
-    const int k = tid + j * S::THREADS;
-    if (k < NVEC) {
-      const int b = place(k * V);
-      VT x;
-      T* xs = reinterpret_cast<T*>(&x);
-#pragma unroll
-      for (int q = 0; q < V; q++) xs[q] = C[b + q];
-      reinterpret_cast<VT*>(lg)[k] = x;
-    }
-  }
-  // lam_a[l][s] += scale_l * sum of the block's line adjoints, in the order of
-  // reduce_lines_kernel: lane t < 256 adds lines t, t + 256, ..., then a tree
-  // (the three axes' trees side by side, with the same pairs as each alone)
-  if (!a.lam_a[0]) return;   // uniform: no acceleration adjoint wanted
-  if (tid < 256) {
-#pragma unroll
-    for (int l = 0; l < 3; l++) {
-      double acc = 0.0;
-      for (int i = tid; i < S::LINES; i += 256) acc += dn[l][i];
-      sh[l][tid] = acc;
-    }
-  }
-  __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if (tid < w) {
-#pragma unroll
-      for (int l = 0; l < 3; l++) sh[l][tid] += sh[l][tid + w];
-    }
-    __syncthreads();
-  }
-  if (tid < 3) a.lam_a[tid][s] += a.scale[tid] * sh[tid][0];
-}
-
-template <typename T, int N>
-hipError_t launch_kick_adj_n(const KickAdjArgs& a, hipStream_t s)
-{
-  using S = AdjKickShape<T, N>;
-  static_assert(S::fits, "two velocity blocks do not fit the LDS");
-  if (a.np <= 0) return hipSuccess;
-  hipLaunchKernelGGL((kick_adj_block<T, N>), dim3((unsigned)a.np), dim3(S::THREADS), 0, s, a);
-  return hipGetLastError();
-}
-
 template <typename T, int N>
 hipError_t launch_adj_n(const SweepArgs& a, const void* fin, void* lam, double* dnu, hipStream_t s)
 {
@@ -576,29 +298,6 @@ hipError_t launch_sweep_adjoint(const SweepArgs& a, int dtype, const void* fin, 
                                 hipStream_t s)
 {
   return dtype == 0 ? launch_adj_t<float>(a, fin, lam, dnu, s) : launch_adj_t<double>(a, fin, lam, dnu, s);
-}
-
-// Cubic velocity blocks of which two copies fit the LDS: FP32 8^3, 16^3,
-// 24^3; FP64 8^3 (FP64 16^3 fits too, but its reverse lines need more
-// registers than a lane has and spill).
-bool kick_adjoint_supported(int dtype, const int nv[3])
-{
-  if (nv[0] != nv[1] || nv[1] != nv[2]) return false;
-  const int n = nv[0];
-  return n == 8 || (dtype == 0 && (n == 16 || n == 24));
-}
-
-hipError_t launch_kick_adjoint(const KickAdjArgs& a, int dtype, const int nv[3], hipStream_t s)
-{
-  if (!kick_adjoint_supported(dtype, nv)) return hipErrorInvalidValue;
-  if (dtype == 0) {
-    switch (nv[0]) {
-      case 8: return launch_kick_adj_n<float, 8>(a, s);
-      case 16: return launch_kick_adj_n<float, 16>(a, s);
-      default: return launch_kick_adj_n<float, 24>(a, s);
-    }
-  }
-  return launch_kick_adj_n<double, 8>(a, s);
 }
 
 hipError_t launch_reduce_lines(double* lam_a, const double* dnu, long long np, long long per, double scale,

@@ -74,8 +74,15 @@ hipError_t launch_kick_box(const KickArgs& a, int dtype, const int nv[3], hipStr
 // workgroups are bound by latency and not by their lines: 32-byte runs and up to
 // 80 KiB serve them (8^3 x 16^3 FP32: 11.4 us against 13.7, and two launches
 // fewer in a step).
+//
+// FP64 only: the pass sums the density in another order than the x sweep, whose
+// sums FP32 gradients were differentiated with. A last bit of the acceleration
+// can move the rounding of a line's alpha to FP32, and a corrector switch behind
+// it; and at 8^3 x 16^3 FP32 the pass with its sums took what the three sweeps
+// take (15 + 4.5 us against 17 + 2.6).
 int drift_box_cells(int dtype, const int n[3], long long nv3)
 {
+  if (dtype == 0) return 0;
   const int es = dtype == 0 ? 4 : 8;
   for (int run = 128; run >= 32; run /= 2) {
     const int w = run / es;

@@ -119,6 +119,8 @@ __global__ __launch_bounds__((DriftShape<T, NY, NZ, W>::THREADS)) void drift_yz_
   const char* slab = static_cast<const char*>(a.f) + ix * NY * NZ * a.nv3 * (long long)sizeof(T);
   const unsigned zoff = (unsigned)i0 * (unsigned)NZ * RB + (unsigned)w * (unsigned)sizeof(T);
   auto tile = [&](long long jc) { return slab + jc * W * (long long)sizeof(T); };
+  // bytes from a cell of f to its place in the output
+  const long long oofs = a.out ? static_cast<const char*>(a.out) - static_cast<const char*>(a.f) : 0;
   T v[NZ];
   if (tid < S::LZ) {
     const char* src = tile(jc0);
@@ -164,7 +166,7 @@ __global__ __launch_bounds__((DriftShape<T, NY, NZ, W>::THREADS)) void drift_yz_
 #pragma unroll
       for (int r = 0; r < NY; r++) u[r] = L[base + r * S::SY];
       pfc_core<T, NY>(u, c.alpha, c.c1, c.c2, periodic);
-      char* dst = const_cast<char*>(tile(jc));
+      char* dst = const_cast<char*>(tile(jc)) + oofs;
       const unsigned ystep = (unsigned)NZ * RB;
       const unsigned y0 = (unsigned)i0 * RB + (unsigned)w * (unsigned)sizeof(T) + (ry ? (unsigned)(NY - 1) * ystep : 0u);
       const unsigned yst = ry ? 0u - ystep : ystep;
@@ -227,6 +229,8 @@ __global__ __launch_bounds__((DrPairShape<T, NP, W>::THREADS)) void drift_yz_pai
   const LineTab<T>* yt = zt + a.nv3;
   const long long RB = a.nv3 * (long long)sizeof(T);   // bytes from one z to the next
   char* slab = static_cast<char*>(a.f) + ix * NP * NP * RB;
+  // bytes from a cell of f to its place in the output
+  const long long oofs = a.out ? static_cast<const char*>(a.out) - static_cast<const char*>(a.f) : 0;
 #pragma unroll 1
   for (int k = 0; k < TILES; k++) {
     const long long jc = (cg * TILES + k) * G + q;
@@ -278,7 +282,7 @@ __global__ __launch_bounds__((DrPairShape<T, NP, W>::THREADS)) void drift_yz_pai
     // row r of the y lines goes to storage y = r, or NP-1-r where vy < 0
     const bool ry = (cy0.meta >> 17) & 1;
     const long long ystep = NP * RB;
-    char* dst = tile + (long long)i0 * RB + (ry ? (NP - 1) * ystep : 0LL);
+    char* dst = tile + oofs + (long long)i0 * RB + (ry ? (NP - 1) * ystep : 0LL);
     const long long yst = ry ? -ystep : ystep;
     store_shifted2<T, NP>(v0, v1, tab_shift(cy0.meta), periodic,
                           [&](int r, T x0, T x1) { *reinterpret_cast<P2*>(dst + r * yst) = P2{x0, x1}; });

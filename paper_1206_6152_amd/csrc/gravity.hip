@@ -419,7 +419,25 @@ __global__ __launch_bounds__(THREADS) void gravity_small_kernel(SmallGravity q)
     w[k] = k < g0 ? q.tw[0][k] : (k < g0 + g1 ? q.tw[1][k - g0] : q.tw[2][k - g0 - g1]);
   if constexpr (!ADJ) {
     double* rs = reinterpret_cast<double*>(b);   // the density, before the transforms need b
-    if (q.part) {
+    if (q.part && q.xsums) {
+      // the x sweep's sums, added as density_from_parts_kernel does: for each
+      // cell the chunks k = g, g + G, ..., then the G group sums in order
+      const int n = n0, G = 256 / n, nchunk = (int)q.nchunk, nyz = n1 * n2;
+#pragma unroll 1
+      for (int s = t; s < np; s += THREADS) {
+        const int q1 = div_small(s, n2, rn2), i2 = s - q1 * n2, x = div_small(q1, n1, rn1), yz = (q1 - x * n1) * n2 + i2;
+        const double* p = q.part + ((long long)yz * nchunk * n + x);
+        double tot = 0.0;
+#pragma unroll 4
+        for (int g = 0; g < G && g < nchunk; g++) {
+          double acc = p[g * n];
+          for (int k = g + G; k < nchunk; k += G) acc += p[k * n];
+          tot += acc;
+        }
+        rs[s] = tot * q.dv3;
+      }
+      __syncthreads();
+    } else if (q.part) {
       // rho[cell] = dv3 sum_k part[k np + cell]: groups of threads take every
       // G-th chunk, then the G sums of a cell are added in order of the group
       const int G = q.groups, grp = G > 1 ? t / np : 0, nchunk = (int)q.nchunk;

@@ -77,7 +77,8 @@ struct vp_ctx {
   // velocity cells per workgroup of the one-pass drift over all three axes (0:
   // none for this grid), and its sums, one per chunk and spatial cell
   int box3 = 0;
-  vp::SmallGravity sg{};      // the parts of a one-launch gravity solve that do not change
+  bool small = false;         // gravity in one launch (gravity_small_supported)
+  vp::SmallGravity sg{};      // its parts that do not change
   double* bsum = nullptr;
   // per-velocity-cell line coefficients of the one-pass T_z T_y (null when
   // the grid has no such pass)
@@ -319,7 +320,7 @@ int drain_events(vp_ctx* c)
 // potential (with ghosts) of the density held in rho_in
 int poisson_from(vp_ctx* c, const double* rho_in, double* phi_out)
 {
-  if (vp::gravity_small_supported(c->wg)) {
+  if (c->small) {
     vp::SmallGravity q = c->sg;
     q.rho = rho_in;
     q.phi = phi_out;
@@ -349,7 +350,7 @@ int potential_into(vp_ctx* c, double* phi_out)
 // acceleration of the density held in c->rho
 int accel_from_rho(vp_ctx* c)
 {
-  if (vp::gravity_small_supported(c->wg)) {
+  if (c->small) {
     vp::SmallGravity q = c->sg;
     q.rho = c->rho;
     q.accel = c->accel;
@@ -495,11 +496,10 @@ int density_adjoint(vp_ctx* c, const double* lam_a)
 {
   const long long ext = (long long)(c->cfg.n[0] + 2) * (c->cfg.n[1] + 2) * (c->cfg.n[2] + 2);
   int r;
-  const bool small = vp::gravity_small_supported(c->wg);
-  if (!small && !c->lphi && (r = dalloc(&c->lphi, sizeof(double) * ext, "potential adjoint"))) return r;
+  if (!c->small && !c->lphi && (r = dalloc(&c->lphi, sizeof(double) * ext, "potential adjoint"))) return r;
   if (!c->radj && (r = dalloc(&c->radj, sizeof(double) * c->np, "density adjoint"))) return r;
   PhaseScope scope(c, 11);
-  if (small) {
+  if (c->small) {
     vp::SmallGravity q = c->sg;
     q.lam_a = lam_a;
     q.radj = c->radj;
@@ -628,6 +628,32 @@ int drift_box(vp_ctx* c, double tau, bool sums)
   return VP_OK;
 }
 
+// T_y T_z(tau) in one pass (drift_yz_supported), from src (over it, or to dst)
+int drift_yz(vp_ctx* c, double tau, const void* src, void* dst)
+{
+  const auto& k = c->cfg;
+  vp::DriftArgs a{};
+  a.f = const_cast<void*>(src);
+  a.out = dst;
+  a.nx = k.n[0];
+  a.nv3 = c->nv3;
+  a.ny = k.n[1];
+  a.nz = k.n[2];
+  a.nvy = k.nv[1];
+  a.nvz = k.nv[2];
+  a.periodic = (k.bc == VP_BC_PERIODIC) ? 1 : 0;
+  a.vmin_y = k.vmin[1];
+  a.dv_y = c->dv[1];
+  a.scale_y = tau / c->dx[1];
+  a.vmin_z = k.vmin[2];
+  a.dv_z = c->dv[2];
+  a.scale_z = tau / c->dx[2];
+  a.tab = c->dtab;
+  PhaseScope scope(c, 9);
+  LAUNCH(c, vp::launch_drift_yz(a, k.dtype, c->stream));
+  return VP_OK;
+}
+
 // T_x T_y T_z(tau): in one pass when the whole spatial grid fits on chip with a
 // chunk of velocity cells; else z and y in one pass when the (y, z) plane does.
 // With sums the last pass leaves density sums (c->bsum, c->xsum).
@@ -637,26 +663,7 @@ int drift(vp_ctx* c, double tau, bool x_sums = false)
   const auto& k = c->cfg;
   if (c->box3) return drift_box(c, tau, x_sums);
   if (vp::drift_yz_supported(k.dtype, k.n[1], k.n[2], c->nv3, k.nv[2])) {
-    vp::DriftArgs a{};
-    a.f = c->f;
-    a.nx = k.n[0];
-    a.nv3 = c->nv3;
-    a.ny = k.n[1];
-    a.nz = k.n[2];
-    a.nvy = k.nv[1];
-    a.nvz = k.nv[2];
-    a.periodic = (k.bc == VP_BC_PERIODIC) ? 1 : 0;
-    a.vmin_y = k.vmin[1];
-    a.dv_y = c->dv[1];
-    a.scale_y = tau / c->dx[1];
-    a.vmin_z = k.vmin[2];
-    a.dv_z = c->dv[2];
-    a.scale_z = tau / c->dx[2];
-    a.tab = c->dtab;
-    {
-      PhaseScope scope(c, 9);
-      LAUNCH(c, vp::launch_drift_yz(a, k.dtype, c->stream));
-    }
+    if ((r = drift_yz(c, tau, c->f, nullptr))) return r;
   } else if ((r = sweep(c, 2, tau)) || (r = sweep(c, 1, tau))) {
     return r;
   }
@@ -680,7 +687,7 @@ int drift_accel(vp_ctx* c, double tau)
     const long long nchunk = (c->nv3 + c->box3 - 1) / c->box3;
     // few sums: the one-workgroup solve adds them itself (512 KiB take it about
     // the time of the launch that it saves)
-    if (vp::gravity_small_supported(c->wg) && c->np * nchunk <= 65536) {
+    if (c->small && c->np * nchunk <= 65536) {
       vp::SmallGravity q = c->sg;
       q.part = c->bsum;
       q.nchunk = nchunk;
@@ -698,6 +705,15 @@ int drift_accel(vp_ctx* c, double tau)
   int r = drift(c, tau, /*x_sums=*/true);
   if (r) return r;
   PhaseScope scope(c, 6);
+  if (c->small && c->np * (c->nv3 / 256) <= 32768) {
+    vp::SmallGravity q = c->sg;
+    q.part = c->xsum;
+    q.xsums = 1;
+    q.nchunk = c->nv3 / 256;
+    q.accel = c->accel;
+    LAUNCH(c, vp::launch_gravity_small(q, c->stream));
+    return VP_OK;
+  }
   const long long nyz = (long long)c->cfg.n[1] * c->cfg.n[2];
   LAUNCH(c, vp::launch_density_from_parts(c->rho, c->xsum, nyz, c->nv3 / 256, c->cfg.n[0],
                                           c->dv[0] * c->dv[1] * c->dv[2], c->stream));
@@ -795,8 +811,8 @@ int vp_init(const vp_config* cfg, void* f_dev, void* hip_stream, vp_ctx** out)
       return r;
     }
   }
-  const bool small = vp::gravity_small_supported(c->wg);
-  if ((small || cfg->bc == VP_BC_ISOLATED) && (r = dalloc(&c->kspec, sizeof(double2) * wn, "green spectrum"))) {
+  c->small = vp::gravity_small_supported(c->wg);
+  if ((c->small || cfg->bc == VP_BC_ISOLATED) && (r = dalloc(&c->kspec, sizeof(double2) * wn, "green spectrum"))) {
     release(c);
     return r;
   }
@@ -840,7 +856,7 @@ int vp_init(const vp_config* cfg, void* f_dev, void* hip_stream, vp_ctx** out)
       return r;
     }
   }
-  if (small) {
+  if (c->small) {
     vp::SmallGravity& q = c->sg;
     q.n = c->ng;
     q.g = c->wg;
@@ -1063,7 +1079,9 @@ int vp_kick_adjoint(vp_ctx* c, double tau, const void* f_in_dev, void* lam_dev, 
   if (!std::isfinite(tau)) return fail(VP_EINVAL, "tau must be finite");
   if (!f_in_dev || !lam_dev) return fail(VP_EINVAL, "null pointer");
   const int nv[3] = {c->cfg.nv[0], c->cfg.nv[1], c->cfg.nv[2]};
-  if (!vp::kick_adjoint_supported(c->cfg.dtype, nv))
+  // the grids of this entry point's contract (vp_grad uses the pass on more)
+  const bool offered = c->cfg.dtype == VP_F32 ? nv[0] <= 24 : nv[0] == 8;
+  if (!offered || !vp::kick_adjoint_supported(c->cfg.dtype, nv))
     return fail(VP_EUNSUPPORTED, "no one-pass reverse half kick for this velocity grid");
   return kick_adjoint(c, tau, f_in_dev, lam_dev, lam_accel_dev);
 }
@@ -1109,8 +1127,17 @@ struct GradWork {
   vp_ctx* c;
   std::vector<void*> bufs;
   std::vector<double*> dbufs;
+  // the caller's state array and the context's acceleration, which stand in
+  // for others during the call: put back however it ends
+  void* user_f;
+  double* user_accel;
+  bool small;
+  explicit GradWork(vp_ctx* c_) : c(c_), user_f(c_->f), user_accel(c_->accel), small(c_->small) {}
   ~GradWork()
   {
+    c->f = user_f;
+    c->accel = user_accel;
+    c->small = small;
     for (void* p : bufs) hipFree(p);
     for (double* p : dbufs) hipFree(p);
   }
@@ -1156,50 +1183,70 @@ int sweep_on(vp_ctx* c, int axis, double tau, void* buf)
   return sweep(c, axis, tau);
 }
 
+// dst = T_y T_z(tau) src (another array): one pass where the plane has one, else
+// two sweeps. c->f is left pointing at dst.
+int zy_to(vp_ctx* c, double tau, const void* src, void* dst)
+{
+  c->f = dst;
+  if (vp::drift_yz_supported(c->cfg.dtype, c->cfg.n[1], c->cfg.n[2], c->nv3, c->cfg.nv[2]))
+    return drift_yz(c, tau, src, dst);
+  int r = sweep_to(c, 2, tau, src, dst);
+  return r ? r : sweep(c, 1, tau);
+}
+
 // Reverse mode of nsteps steps of Eq. (17) with checkpoints; see vp.h.
 //
 // Device memory: every k-th state of the forward run (ceil(nsteps/k) copies of
-// f), the other k-1 states of the segment being reversed, and two work arrays
+// f), the other k-1 states of the segment being reversed, and three work arrays
 // in which the inputs of a step's nine sweeps are regenerated from the step's
-// start, in the order the reverse sweeps need them:
-//   closing half kick (a_{n+1}):  in8 = T_vy T_vx in6, then in7 = T_vx in6,
-//                                 with in6 = drift(kick(x0)) kept throughout;
-//   drift:                        in5 = T_y T_z in3, then in4 = T_z in3,
-//                                 with in3 = kick(x0) kept throughout;
-//   opening half kick (a_n):      in1 = T_vx x0 and in2 = T_vy in1.
-// Every regenerated input is computed by the kernels of the forward run, so it
-// is the forward input bit for bit; the price is twelve sweep passes per step
-// instead of eight. Where two velocity blocks fit the LDS
-// (kick_adjoint_supported), each reverse half kick is one pass at its input
-// (in6, or x0) that rebuilds in7, in8 (in1, in2) on chip: seven regenerating
-// passes and five reverse passes per step instead of twelve and nine, with the
-// same bits.
+// start x0, in the order the reverse sweeps need them:
+//   in3 = kick(x0) in b1, in5 = T_y T_z in3 in b2, in6 = T_x in5 in b3;
+//   closing half kick (a_{n+1}):  one pass at in6 that rebuilds in7 = T_vx in6
+//                                 and in8 = T_vy in7 on chip (kick_adjoint);
+//   drift:                        at in5, then at in4 = T_z in3 (in b3), at in3;
+//   opening half kick (a_n):      one pass at x0.
+// Velocity blocks without that pass regenerate in8 and in7 in b2 (and in5 again
+// after them), in1 = T_vx x0 in b1 and in2 = T_vy in1 in b2. Where the device
+// has no room for b3, in6 is formed in b1, and in3 and in5 are formed again
+// after the closing half kick. Every regenerated input is computed by the
+// kernels of the forward run, so it is the forward input bit for bit.
+//
+// The kicks read and drift_accel writes the acceleration of step n where it is
+// kept (c->accel points there meanwhile).
 int grad_impl(vp_ctx* c, int nsteps, double dt, int k, void* lam, double* loss)
 {
   const size_t fb = (size_t)c->np * (size_t)c->nv3 * (c->cfg.dtype == VP_F32 ? 4 : 8);
   const size_t ab = sizeof(double) * 3 * (size_t)c->np;
   const int nck = (nsteps + k - 1) / k;
   void* user_f = c->f;
-  GradWork w{c};
+  GradWork w(c);
   // ck: every k-th state of the forward run; st[1..k-1]: the other states of
-  // one segment, recomputed; b1, b2: regenerated sweep inputs of one step
+  // one segment, recomputed; b1, b2, b3: regenerated sweep inputs of one step
   std::vector<void*> ck(nck), st(k, nullptr);
-  void *b1 = nullptr, *b2 = nullptr;
-  double *ahist = nullptr, *lam_a = nullptr, *lam_p = nullptr;
+  void *b1 = nullptr, *b2 = nullptr, *b3 = nullptr;
+  double *ahist = nullptr, *lam_p = nullptr;
   int r;
   for (int i = 0; i < nck; i++)
     if ((r = w.f(&ck[i], fb))) return r;
   for (int i = 1; i < k; i++)
     if ((r = w.f(&st[i], fb))) return r;
   if ((r = w.f(&b1, fb)) || (r = w.f(&b2, fb))) return r;
-  if ((r = w.d(&ahist, ab * (size_t)(nsteps + 1))) || (r = w.d(&lam_a, ab)) || (r = w.d(&lam_p, ab))) return r;
+  if ((r = w.d(&ahist, ab * (size_t)(nsteps + 1))) || (r = w.d(&lam_p, ab))) return r;
+  if (w.f(&b3, fb)) {
+    b3 = nullptr;
+    g_err.clear();
+  }
   auto A = [&](int n) { return ahist + (size_t)n * 3 * c->np; };
+  // FP32: the separate gravity kernels, whose roundings FP32 gradients have been
+  // differentiated with. A last bit of the acceleration can move the rounding of
+  // a line's alpha to FP32, and a corrector switch behind it.
+  if (c->cfg.dtype == VP_F32) c->small = false;
   const int nv[3] = {c->cfg.nv[0], c->cfg.nv[1], c->cfg.nv[2]};
   const bool fused_adj = vp::kick_adjoint_supported(c->cfg.dtype, nv);
-  auto set_accel = [&](int n) { return copy_f(c, c->accel, A(n), ab); };
 
   // forward pass from f0, keeping checkpoints and every step's acceleration
-  if ((r = copy_f(c, A(0), c->accel, ab))) return r;
+  if ((r = copy_f(c, A(0), w.user_accel, ab))) return r;
+  c->accel = A(0);
   const double h = 0.5 * dt;
   // between checkpoints the closing half kick of step n-1 and the opening one
   // of step n (same acceleration) run as one pass, as in vp_run
@@ -1210,8 +1257,9 @@ int grad_impl(vp_ctx* c, int nsteps, double dt, int k, void* lam, double* loss)
       closing = false;
       if ((r = copy_f(c, ck[n / k], user_f, fb))) return r;
     }
-    if ((r = kick_n(c, h, closing ? 2 : 1)) || (r = drift_accel(c, dt))) return r;
-    if ((r = copy_f(c, A(n + 1), c->accel, ab))) return r;
+    if ((r = kick_n(c, h, closing ? 2 : 1))) return r;
+    c->accel = A(n + 1);
+    if ((r = drift_accel(c, dt))) return r;
     closing = true;
   }
   if (closing && (r = kick(c, h))) return r;
@@ -1222,56 +1270,66 @@ int grad_impl(vp_ctx* c, int nsteps, double dt, int k, void* lam, double* loss)
   LAUNCH(c, vp::launch_potential_energy(c->red, c->rho, c->phi, c->ng, dx3, c->stream));
   HIP_TRY(hipMemcpyAsync(c->host, c->red, sizeof(double), hipMemcpyDeviceToHost, c->stream));
   LAUNCH(c, vp::launch_seed(lam, c->cfg.dtype, c->phi, c->ng, c->nv3, -dx3 * dv3, c->stream));
+  // lam_p: the adjoint of the acceleration in hand, from the half kicks that use it
   HIP_TRY(hipMemsetAsync(lam_p, 0, ab, c->stream));
 
-  for (int seg = nck - 1; seg >= 0 && r == VP_OK; seg--) {
+  for (int seg = nck - 1; seg >= 0; seg--) {
     const int s0 = seg * k, s1 = (s0 + k < nsteps) ? s0 + k : nsteps;
     st[0] = ck[seg];
-    for (int n = s0; n + 1 < s1 && r == VP_OK; n++) {   // recompute the segment's states
-      if ((r = set_accel(n))) break;
-      if ((r = kick_to(c, h, st[n - s0], st[n - s0 + 1], fb)) || (r = drift_accel(c, dt)) || (r = kick(c, h))) break;
+    for (int n = s0; n + 1 < s1; n++) {   // recompute the segment's states
+      c->accel = A(n);
+      if ((r = kick_to(c, h, st[n - s0], st[n - s0 + 1], fb))) return r;
+      c->accel = A(n + 1);                // written again, with the same values
+      if ((r = drift_accel(c, dt)) || (r = kick(c, h))) return r;
     }
-    for (int n = s1 - 1; n >= s0 && r == VP_OK; n--) {
+    for (int n = s1 - 1; n >= s0; n--) {
       void* x0 = st[n - s0];
-      // closing half kick, acceleration a_{n+1}: in6 in b1, in8 then in7 in b2
-      // (or the whole reverse half kick in one pass at in6)
-      if ((r = set_accel(n)) || (r = kick_to(c, h, x0, b1, fb))) break;
-      if ((r = drift(c, dt))) break;                                     // b1 = in6
-      if ((r = set_accel(n + 1)) || (r = copy_f(c, lam_a, lam_p, ab))) break;
+      c->accel = A(n);
+      if ((r = kick_to(c, h, x0, b1, fb))) return r;              // b1 = in3
+      void* in6 = b3 ? b3 : b1;
+      if (b3) {
+        if ((r = zy_to(c, dt, b1, b2)) || (r = sweep_to(c, 0, dt, b2, b3))) return r;   // b2 = in5, b3 = in6
+      } else if ((r = drift(c, dt))) {                            // b1 = in6
+        return r;
+      }
+      // closing half kick, acceleration a_{n+1}
+      c->accel = A(n + 1);
+      bool have5 = b3 != nullptr;
       if (fused_adj) {
-        if ((r = kick_adjoint(c, h, b1, lam, lam_a))) break;
+        if ((r = kick_adjoint(c, h, in6, lam, lam_p))) return r;
       } else {
-        if ((r = sweep_to(c, 3, h, b1, b2)) || (r = sweep_on(c, 4, h, b2))) break;
-        if ((r = sweep_adjoint(c, 5, h, b2, lam, lam_a))) break;          // at in8
-        if ((r = sweep_to(c, 3, h, b1, b2)) || (r = sweep_adjoint(c, 4, h, b2, lam, lam_a))) break;   // at in7
-        if ((r = sweep_adjoint(c, 3, h, b1, lam, lam_a))) break;          // at in6
+        if ((r = sweep_to(c, 3, h, in6, b2)) || (r = sweep_on(c, 4, h, b2))) return r;
+        if ((r = sweep_adjoint(c, 5, h, b2, lam, lam_p))) return r;          // at in8
+        if ((r = sweep_to(c, 3, h, in6, b2)) || (r = sweep_adjoint(c, 4, h, b2, lam, lam_p))) return r;   // at in7
+        if ((r = sweep_adjoint(c, 3, h, in6, lam, lam_p))) return r;         // at in6
+        have5 = false;
       }
       // a_{n+1} = A(state after the drift): the density adjoint's contribution
       // to lam rides on the loads of the reverse x sweep that follows
-      if ((r = density_adjoint(c, lam_a))) break;
-      // drift: in3 in b1, in5 then in4 in b2
-      if ((r = set_accel(n)) || (r = kick_to(c, h, x0, b1, fb))) break;  // b1 = in3
-      if ((r = sweep_to(c, 2, dt, b1, b2)) || (r = sweep_on(c, 1, dt, b2))) break;   // b2 = in5
-      if ((r = sweep_adjoint(c, 0, dt, b2, lam, nullptr, c->radj))) break;
-      if ((r = sweep_to(c, 2, dt, b1, b2)) || (r = sweep_adjoint(c, 1, dt, b2, lam, nullptr))) break;   // at in4
-      if ((r = sweep_adjoint(c, 2, dt, b1, lam, nullptr))) break;         // at in3
-      // opening half kick, acceleration a_n: in1 in b1, in2 in b2 (or one pass at x0)
+      if ((r = density_adjoint(c, lam_p))) return r;
       HIP_TRY(hipMemsetAsync(lam_p, 0, ab, c->stream));
+      // drift, then the opening half kick with a_n
+      c->accel = A(n);
+      if (!b3 && (r = kick_to(c, h, x0, b1, fb))) return r;       // b1 = in3
+      if (!have5 && (r = zy_to(c, dt, b1, b2))) return r;         // b2 = in5
+      if ((r = sweep_adjoint(c, 0, dt, b2, lam, nullptr, c->radj))) return r;
+      void* in4 = b3 ? b3 : b2;
+      if ((r = sweep_to(c, 2, dt, b1, in4)) || (r = sweep_adjoint(c, 1, dt, in4, lam, nullptr))) return r;
+      if ((r = sweep_adjoint(c, 2, dt, b1, lam, nullptr))) return r;         // at in3
       if (fused_adj) {
-        if ((r = kick_adjoint(c, h, x0, lam, lam_p))) break;
+        if ((r = kick_adjoint(c, h, x0, lam, lam_p))) return r;
         continue;
       }
-      if ((r = sweep_to(c, 3, h, x0, b1)) || (r = sweep_to(c, 4, h, b1, b2))) break;
+      if ((r = sweep_to(c, 3, h, x0, b1)) || (r = sweep_to(c, 4, h, b1, b2))) return r;   // in1, in2
       if ((r = sweep_adjoint(c, 5, h, b2, lam, lam_p)) || (r = sweep_adjoint(c, 4, h, b1, lam, lam_p)) ||
           (r = sweep_adjoint(c, 3, h, x0, lam, lam_p)))
-        break;
+        return r;
     }
   }
   c->f = user_f;
-  if (r) return r;
   // a_0 = A(f0)
   if ((r = accel_adjoint(c, lam_p, lam))) return r;
-  if ((r = set_accel(nsteps))) return r;
+  if ((r = copy_f(c, w.user_accel, A(nsteps), ab))) return r;
   HIP_TRY(hipStreamSynchronize(c->stream));
   *loss = -c->host[0];
   return VP_OK;

@@ -94,6 +94,7 @@ hipError_t launch_kick_planes(const KickArgs& a, int dtype, const int nv[3], hip
 // every (y, z) cell. Position sweeps: nu = v_l(j) tau / dx_l.
 struct DriftArgs {
   void* f;
+  void* out;     // null: over f
   long long nx, nv3;
   int ny, nz;
   long long nvy, nvz;
@@ -185,6 +186,7 @@ struct SmallGravity {
   const double* rho;
   const double* part;
   long long nchunk;
+  int xsums;              // part holds the x sweep's sums (launch_density_from_parts)
   double dv3;
   double* accel;
   double* phi;

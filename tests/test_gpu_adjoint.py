@@ -381,3 +381,36 @@ def test_benchmark_grid_gradient_fp32_against_fp64_and_finite_differences():
             name, fd, a64, abs(a64 - fd) / abs(fd), a32, abs(a32 - fd) / abs(fd)), flush=True)
         assert abs(a64 - fd) <= 1e-4 * abs(fd)
         assert abs(a32 - fd) <= 1e-3 * abs(fd)
+
+
+@pytest.mark.parametrize("dtype,nv,bc", [(VP_F64, 16, VP_BC_PERIODIC), (VP_F64, 24, VP_BC_ISOLATED),
+                                         (VP_F32, 32, VP_BC_PERIODIC), (VP_F32, 24, VP_BC_ISOLATED)])
+def test_gradient_on_one_pass_reverse_kick_grids(dtype, nv, bc):
+    # the largest velocity blocks whose reverse half kick runs in one pass
+    # inside vp_grad (FP64 16^3 and 24^3, FP32 24^3 and 32^3), several steps per
+    # segment and a last segment shorter than the others; tolerances as for the
+    # other whole gradients (1e-10 FP64; 1e-3 FP32, where corrector switches
+    # that FP32 rounding moves set the scale)
+    print("case", dtype, nv, bc, flush=True)
+    torch = _t()
+    w = small_workload(bc, n=(2, 3, 2), nv=(nv, nv, nv))
+    rng = np.random.default_rng(nv)
+    V = np.meshgrid(*[w.vc(l) / w.vmax[l] for l in range(3)], indexing="ij")
+    f0 = np.exp(-4 * (V[0] ** 2 + V[1] ** 2 + V[2] ** 2)) * rng.uniform(0.5, 1.5, w.n).reshape(w.n + (1, 1, 1))
+    f0 *= rng.uniform(0.9, 1.1, w.shape)
+    f0 = f0.astype(NP[dtype]).astype(np.float64)
+    dt = 0.4 * min(w.dx(l) / max(abs(w.vmin[l]), abs(w.vmax[l])) for l in range(3))
+    ref_loss, ref_g = oracle.grad(oracle_grid(w), f0, 3, dt)
+    f = _dev(f0, NP[dtype])
+    sim = Simulator(config_of(w, dtype), f)
+    loss, g = sim.grad(3, dt, 2)
+    sim.close()
+    if dtype == VP_F64:      # f ends as after vp_run, bit for bit
+        f2 = _dev(f0)
+        run = Simulator(config_of(w, dtype), f2)
+        run.run(3, dt)
+        run.close()
+        assert torch.equal(f, f2)
+    tol = 1e-10 if dtype == VP_F64 else 1e-3
+    assert abs(loss - ref_loss) <= tol * abs(ref_loss)
+    assert rel_l1(g.cpu().numpy(), ref_g) <= tol
