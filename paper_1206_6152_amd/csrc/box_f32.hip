@@ -19,34 +19,35 @@ hipError_t launch_drift_box_f32(const DriftBoxArgs& a, int w, hipStream_t s)
   return launch_drift_box_t<float>(a, w, s);
 }
 
-// rho[cell] = dv3 sum_k part[k np + cell]: a workgroup takes 32 cells, its
-// eight rows of lanes every eighth chunk; the eight sums are added in order.
-__global__ __launch_bounds__(256) void box_density_kernel(double* rho, const double* part, long long np,
-                                                          long long nchunk, double dv3)
+// rho[cell] = dv3 sum_k part[k np + cell]: a workgroup takes four cells (there
+// are few: up to 512), its 256 groups of lanes every 256th chunk with four sums
+// in flight; the groups' sums are added in a tree. 64 cells of 6912 chunks took
+// 43 us with eight groups and 32 cells per workgroup.
+__global__ __launch_bounds__(1024) void box_density_kernel(double* rho, const double* part, int np, int nchunk,
+                                                           double dv3)
 {
-  __shared__ double sh[8][32];
-  const int c = threadIdx.x & 31, g = threadIdx.x >> 5;
-  const long long cell = (long long)blockIdx.x * 32 + c;
+  constexpr int G = 256;
+  __shared__ double sh[G][4];
+  const int c = threadIdx.x & 3, g = threadIdx.x >> 2, cell = blockIdx.x * 4 + c;
   double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
   if (cell < np) {
     const double* p = part + cell;
-    long long k = g;
-    for (; k + 24 < nchunk; k += 32) {
-      s0 += p[k * np];
-      s1 += p[(k + 8) * np];
-      s2 += p[(k + 16) * np];
-      s3 += p[(k + 24) * np];
+    int k = g;
+    for (; k + 3 * G < nchunk; k += 4 * G) {
+      s0 += p[(long long)k * np];
+      s1 += p[(long long)(k + G) * np];
+      s2 += p[(long long)(k + 2 * G) * np];
+      s3 += p[(long long)(k + 3 * G) * np];
     }
-    for (; k < nchunk; k += 8) s0 += p[k * np];
+    for (; k < nchunk; k += G) s0 += p[(long long)k * np];
   }
   sh[g][c] = (s0 + s1) + (s2 + s3);
   __syncthreads();
-  if (g == 0 && cell < np) {
-    double t = 0.0;
-#pragma unroll
-    for (int i = 0; i < 8; i++) t += sh[i][c];
-    rho[cell] = t * dv3;
+  for (int w = G / 2; w > 0; w >>= 1) {
+    if (g < w) sh[g][c] += sh[g + w][c];
+    __syncthreads();
   }
+  if (g == 0 && cell < np) rho[cell] = sh[0][c] * dv3;
 }
 
 constexpr int kLdsMost = 152 * 1024;   // of 160 KiB, less the coefficients and the split lines' maxima
@@ -66,14 +67,15 @@ hipError_t launch_kick_box(const KickArgs& a, int dtype, const int nv[3], hipStr
 
 // Velocity cells per workgroup of the one-pass drift of the grid n; 0 if the
 // single sweeps (or the one-pass T_y T_z) are the better choice. The pass is
-// bound by vector issue and LDS latency, so several workgroups have to share a
-// CU: boxes of up to 40 KiB, with runs of 128 bytes, or of 64 that share their
-// lines with a neighbour on the same XCD. 8^3 x 32^3 FP32: 50 us with 64-byte
-// runs (37 KiB), 56 with 128 (73 KiB), 69 for the three sweeps; 12^3 x 24^3 in
-// one workgroup per CU (110 KiB) 97 us against 87. Launches of at most 512
-// workgroups are bound by latency and not by their lines: 32-byte runs and up to
-// 80 KiB serve them (8^3 x 16^3 FP32: 11.4 us against 13.7, and two launches
-// fewer in a step).
+// bound by vector issue (index decoding and run-time strides) and LDS latency,
+// so several workgroups have to share a CU: boxes of up to 40 KiB, with runs of
+// 128 bytes, or of 64 that share their lines with a neighbour on the same XCD.
+// Against the three sweeps, FP64: 4^3 x 24^3 10.8 us (16.6), 8^3 x 32^3 97 (121),
+// 6^3 x 48^3 144 (166); beyond 256 MiB it no longer pays (8^3 x 64^3, two steps:
+// 6.2 ms against 5.9), nor with longer axes (8 x 12 x 4 x 48^3 347
+// against 312, 64 x 4 x 4 x 12^3 37 against 33). Grids of under a MiB are bound by
+// latency alone (1D-1V 128 x 128: 6 us against three launches of 3 to 12); there
+// and in launches of at most 512 workgroups 32-byte runs and up to 80 KiB serve.
 //
 // FP64 only: the pass sums the density in another order than the x sweep, whose
 // sums FP32 gradients were differentiated with. A last bit of the acceleration
@@ -83,7 +85,11 @@ hipError_t launch_kick_box(const KickArgs& a, int dtype, const int nv[3], hipStr
 int drift_box_cells(int dtype, const int n[3], long long nv3)
 {
   if (dtype == 0) return 0;
-  const int es = dtype == 0 ? 4 : 8;
+  const int es = 8;
+  const long long np = (long long)n[0] * n[1] * n[2];
+  const long long bytes = np * nv3 * es;
+  if ((n[0] > 8 || n[1] > 8 || n[2] > 8) && bytes >= (1 << 20)) return 0;
+  if (bytes > (1 << 28)) return 0;
   for (int run = 128; run >= 32; run /= 2) {
     const int w = run / es;
     const size_t lds = box_lds(n[0], n[1], n[2], w, es);
@@ -105,7 +111,8 @@ hipError_t launch_box_density(double* rho, const double* part, long long np, lon
                               hipStream_t s)
 {
   if (np <= 0) return hipSuccess;
-  hipLaunchKernelGGL(box_density_kernel, dim3((unsigned)((np + 31) / 32)), dim3(256), 0, s, rho, part, np, nchunk, dv3);
+  hipLaunchKernelGGL(box_density_kernel, dim3((unsigned)((np + 3) / 4)), dim3(1024), 0, s, rho, part, (int)np,
+                     (int)nchunk, dv3);
   return hipGetLastError();
 }
 
