@@ -708,11 +708,14 @@ struct alignas(sizeof(T) * V) Pack {
 };
 
 // Per spatial cell: sum_j f_j and sum_j f_j |v_j|^2 over its velocity block
-// (Eqs. (29), (30) before the dx^3 dv^3 factor). A lane loads V consecutive
+// (Eqs. (29), (30) before the dx^3 dv^3 factor), and the density of Eq. (18) from
+// the first: the energies take one pass over f instead of this one and
+// density_kernel's (32^3 x 32^3 FP32: 0.69 ms each, at the rate of a read). A lane loads V consecutive
 // cells of one vz-line at a time (16 bytes when nv_z is a multiple of V, else
 // V = 1), four loads in flight, and walks the velocity indices with Idx3.
 template <typename T, int V>
-__global__ __launch_bounds__(RED) void energy_partial_kernel(const T* f, double* part, VelGrid vg)
+__global__ __launch_bounds__(RED) void energy_partial_kernel(const T* f, double* part, double* rho, VelGrid vg,
+                                                              double dv3)
 {
   __shared__ double sh[RED];
   const int ny = vg.nv[1], nz = vg.nv[2];
@@ -749,6 +752,7 @@ __global__ __launch_bounds__(RED) void energy_partial_kernel(const T* f, double*
   if (threadIdx.x == 0) {
     part[2 * (long long)blockIdx.x] = ms;
     part[2 * (long long)blockIdx.x + 1] = ks;
+    rho[blockIdx.x] = ms * dv3;
   }
 }
 
@@ -813,7 +817,7 @@ __global__ __launch_bounds__(RED) void energy_final_kernel(double* out, int nb, 
   }
 }
 
-__global__ __launch_bounds__(RED) void accel_max_stage_kernel(double* out, const double* a, long long np, double i0,
+__global__ __launch_bounds__(RED) void accel_max_stage_kernel(double* part, const double* a, long long np, double i0,
                                                               double i1, double i2)
 {
   __shared__ double sh[RED];
@@ -824,16 +828,16 @@ __global__ __launch_bounds__(RED) void accel_max_stage_kernel(double* out, const
     m = fmax(m, fabs(a[2 * np + s]) * i2);
   }
   const double r = block_max(m, sh);
-  if (threadIdx.x == 0) out[RED_PART + blockIdx.x] = r;
+  if (threadIdx.x == 0) part[blockIdx.x] = r;
 }
 
-__global__ __launch_bounds__(RED) void max_final_kernel(double* out, int nb)
+__global__ __launch_bounds__(RED) void max_final_kernel(double* dst, const double* part, int nb)
 {
   __shared__ double sh[RED];
   double m = 0.0;
-  for (int b = threadIdx.x; b < nb; b += RED) m = fmax(m, out[RED_PART + b]);
+  for (int b = threadIdx.x; b < nb; b += RED) m = fmax(m, part[b]);
   const double r = block_max(m, sh);
-  if (threadIdx.x == 0) out[0] = r;
+  if (threadIdx.x == 0) *dst = r;
 }
 
 // ---- transposes for the reverse mode ---------------------------------------
@@ -1295,25 +1299,27 @@ hipError_t launch_gradient(double* accel, const double* phi_ext, Grid3 n, double
   return hipGetLastError();
 }
 
-hipError_t launch_energy_partials(const void* f, int dtype, double* part, long long np, VelGrid vg, hipStream_t s)
+hipError_t launch_energy_partials(const void* f, int dtype, double* part, double* rho, long long np, VelGrid vg,
+                                  hipStream_t s)
 {
   // 16-byte groups need whole groups per vz-line and a 16-byte aligned base
   // (every block then starts aligned, its length being a multiple of V).
   const bool a16 = (reinterpret_cast<uintptr_t>(f) % 16) == 0;
+  const double dv3 = vg.dv[0] * vg.dv[1] * vg.dv[2];
   if (dtype == 0) {
     if (a16 && vg.nv[2] % 4 == 0)
       hipLaunchKernelGGL((energy_partial_kernel<float, 4>), dim3((unsigned)np), dim3(RED), 0, s,
-                         static_cast<const float*>(f), part, vg);
+                         static_cast<const float*>(f), part, rho, vg, dv3);
     else
       hipLaunchKernelGGL((energy_partial_kernel<float, 1>), dim3((unsigned)np), dim3(RED), 0, s,
-                         static_cast<const float*>(f), part, vg);
+                         static_cast<const float*>(f), part, rho, vg, dv3);
   } else {
     if (a16 && vg.nv[2] % 2 == 0)
       hipLaunchKernelGGL((energy_partial_kernel<double, 2>), dim3((unsigned)np), dim3(RED), 0, s,
-                         static_cast<const double*>(f), part, vg);
+                         static_cast<const double*>(f), part, rho, vg, dv3);
     else
       hipLaunchKernelGGL((energy_partial_kernel<double, 1>), dim3((unsigned)np), dim3(RED), 0, s,
-                         static_cast<const double*>(f), part, vg);
+                         static_cast<const double*>(f), part, rho, vg, dv3);
   }
   return hipGetLastError();
 }
@@ -1327,12 +1333,15 @@ hipError_t launch_energy_final(double* out, const double* part, const double* rh
   return hipGetLastError();
 }
 
-hipError_t launch_accel_max(double* out, const double* accel, long long np, double i0, double i1, double i2,
-                            hipStream_t s)
+// One workgroup takes up to 4096 cells (each lane 16) in the time of a launch;
+// larger grids take the two stages.
+hipError_t launch_accel_max(double* work, double* dst, const double* accel, long long np, double i0, double i1,
+                            double i2, hipStream_t s)
 {
-  const int nb = reduce_blocks(np);
-  hipLaunchKernelGGL(accel_max_stage_kernel, dim3(nb), dim3(RED), 0, s, out, accel, np, i0, i1, i2);
-  hipLaunchKernelGGL(max_final_kernel, dim3(1), dim3(RED), 0, s, out, nb);
+  const int nb = np <= 4096 ? 1 : reduce_blocks(np);
+  hipLaunchKernelGGL(accel_max_stage_kernel, dim3(nb), dim3(RED), 0, s, nb == 1 ? dst : work + RED_PART, accel, np, i0,
+                     i1, i2);
+  if (nb > 1) hipLaunchKernelGGL(max_final_kernel, dim3(1), dim3(RED), 0, s, dst, work + RED_PART, nb);
   return hipGetLastError();
 }
 

@@ -606,13 +606,14 @@ int kick_n(vp_ctx* c, double tau, int reps)
 
 int kick(vp_ctx* c, double tau) { return kick_n(c, tau, 1); }
 
-// T_x T_y T_z(tau) over chunks of velocity cells (box.h); with sums the chunks'
-// density sums go to c->bsum
-int drift_box(vp_ctx* c, double tau, bool sums)
+// T_x T_y T_z(tau) over chunks of velocity cells (box.h), from src (over it, or
+// to dst); with sums the chunks' density sums go to c->bsum
+int drift_box(vp_ctx* c, double tau, bool sums, const void* src, void* dst)
 {
   const auto& k = c->cfg;
   vp::DriftBoxArgs a{};
-  a.f = c->f;
+  a.f = src;
+  a.out = dst;
   a.nv3 = c->nv3;
   a.periodic = (k.bc == VP_BC_PERIODIC) ? 1 : 0;
   a.part = sums ? c->bsum : nullptr;
@@ -661,7 +662,7 @@ int drift(vp_ctx* c, double tau, bool x_sums = false)
 {
   int r;
   const auto& k = c->cfg;
-  if (c->box3) return drift_box(c, tau, x_sums);
+  if (c->box3) return drift_box(c, tau, x_sums, c->f, nullptr);
   if (vp::drift_yz_supported(k.dtype, k.n[1], k.n[2], c->nv3, k.nv[2])) {
     if ((r = drift_yz(c, tau, c->f, nullptr))) return r;
   } else if ((r = sweep(c, 2, tau)) || (r = sweep(c, 1, tau))) {
@@ -1019,14 +1020,14 @@ int vp_energy(vp_ctx* c, double out_host[4])
   int r = check_ctx(c);
   if (r) return r;
   if (!out_host) return fail(VP_EINVAL, "null pointer");
-  if ((r = potential_into(c, c->phi))) return r;
   vp::VelGrid vg{};
   for (int l = 0; l < 3; l++) {
     vg.nv[l] = c->cfg.nv[l];
     vg.vmin[l] = c->cfg.vmin[l];
     vg.dv[l] = c->dv[l];
   }
-  LAUNCH(c, vp::launch_energy_partials(c->f, c->cfg.dtype, c->part, c->np, vg, c->stream));
+  LAUNCH(c, vp::launch_energy_partials(c->f, c->cfg.dtype, c->part, c->rho, c->np, vg, c->stream));
+  if ((r = poisson_from(c, c->rho, c->phi))) return r;
   LAUNCH(c, vp::launch_energy_final(c->red, c->part, c->rho, c->phi, c->ng, c->dx[0] * c->dx[1] * c->dx[2],
                                     c->dv[0] * c->dv[1] * c->dv[2], c->stream));
   HIP_TRY(hipMemcpyAsync(c->host, c->red, sizeof(double) * 4, hipMemcpyDeviceToHost, c->stream));
@@ -1044,9 +1045,9 @@ int vp_dt(vp_ctx* c, double cfl, double* dt_host)
   if (r) return r;
   if (!dt_host) return fail(VP_EINVAL, "null pointer");
   if (!(std::isfinite(cfl) && cfl > 0)) return fail(VP_EINVAL, "cfl must be finite and > 0");
-  LAUNCH(c, vp::launch_accel_max(c->red, c->accel, c->np, 1.0 / c->dv[0], 1.0 / c->dv[1], 1.0 / c->dv[2],
+  // the maximum goes straight to the pinned page that the host reads
+  LAUNCH(c, vp::launch_accel_max(c->red, c->host, c->accel, c->np, 1.0 / c->dv[0], 1.0 / c->dv[1], 1.0 / c->dv[2],
                                  c->stream));
-  HIP_TRY(hipMemcpyAsync(c->host, c->red, sizeof(double), hipMemcpyDeviceToHost, c->stream));
   HIP_TRY(hipStreamSynchronize(c->stream));
   double dtp = INFINITY;
   for (int l = 0; l < 3; l++) {
@@ -1287,7 +1288,9 @@ int grad_impl(vp_ctx* c, int nsteps, double dt, int k, void* lam, double* loss)
       c->accel = A(n);
       if ((r = kick_to(c, h, x0, b1, fb))) return r;              // b1 = in3
       void* in6 = b3 ? b3 : b1;
-      if (b3) {
+      if (b3 && c->box3 && !fused_adj) {   // in5 is not kept
+        if ((r = drift_box(c, dt, false, b1, b3))) return r;
+      } else if (b3) {
         if ((r = zy_to(c, dt, b1, b2)) || (r = sweep_to(c, 0, dt, b2, b3))) return r;   // b2 = in5, b3 = in6
       } else if ((r = drift(c, dt))) {                            // b1 = in6
         return r;

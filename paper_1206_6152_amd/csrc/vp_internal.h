@@ -227,13 +227,14 @@ hipError_t launch_extract_phi(double* phi_ext, Grid3 n, const double2* data, Gri
 hipError_t launch_gradient(double* accel, const double* phi_ext, Grid3 n, double d0, double d1,
                            double d2, hipStream_t s);
 
-// Partial sums per spatial cell: part[2*s] = sum f, part[2*s+1] = sum f |v|^2.
+// Partial sums per spatial cell: part[2*s] = sum f, part[2*s+1] = sum f |v|^2,
+// and rho[s] = dv^3 sum f.
 struct VelGrid {
   int nv[3];
   double vmin[3];
   double dv[3];
 };
-hipError_t launch_energy_partials(const void* f, int dtype, double* part, long long np,
+hipError_t launch_energy_partials(const void* f, int dtype, double* part, double* rho, long long np,
                                   VelGrid vg, hipStream_t s);
 
 // The whole-grid reductions below take a device buffer `out` of
@@ -248,8 +249,9 @@ hipError_t launch_energy_final(double* out, const double* part, const double* rh
                                const double* phi_ext, Grid3 n, double dx3, double dv3,
                                hipStream_t s);
 
-// out[0] = max over cells and axes of |a_l| * inv_dv[l].
-hipError_t launch_accel_max(double* out, const double* accel, long long np, double i0, double i1,
+// *dst (device memory, or the host's pinned memory) = max over cells and axes of
+// |a_l| * inv_dv[l]; work as `out` above.
+hipError_t launch_accel_max(double* work, double* dst, const double* accel, long long np, double i0, double i1,
                             double i2, hipStream_t s);
 
 // ---- reverse mode -------------------------------------------------------------
