@@ -14,10 +14,26 @@ namespace {
 
 // ---- line coefficients of a half kick, per spatial cell ----------------------
 // The three velocity sweeps of a spatial cell move with nu_l = a_l tau / dv_l,
-// uniform over its velocity block. kick_table_kernel splits each |nu_l| once
-// per call (line_coef, as every sweep does, so the bits agree) and the kick
-// passes read the entry of their block instead of repeating the FP64
-// arithmetic in every lane.
+// uniform over its velocity block. Lanes 0..2 of every wave split |nu_l| while
+// the wave's first loads are in flight (line_coef, as every sweep does, so the
+// bits agree), and the values are handed round in scalar registers: a table
+// filled by a launch of its own costs that launch on every call (3 to 5 us,
+// where the 8^3 x 16^3 pass itself takes 6).
+template <typename T>
+struct KickCoefs {
+  LineCoef<T> c;     // of axis min(lane, 2)
+  __device__ __forceinline__ LineCoef<T> axis(int l) const
+  {
+    return LineCoef<T>{of_lane(c.alpha, l), of_lane(c.c1, l), of_lane(c.c2, l), of_lane(c.shift, l), false};
+  }
+};
+
+// The passes over larger blocks (kick_pair_block, kick_vxvy_pairs,
+// kick_lines_f64) do read a table: slices share a block, a workgroup alone on
+// its CU has little to hide the split behind, and against their passes the
+// launch is nothing (24^3 x 48^3 FP32: vz-slices 2.5 ms with the table, 3.1
+// without, vx-slices 2.43 and 2.55; a step of 32^3 x 32^3 FP64 0.3 % less with
+// it).
 template <typename T>
 struct KickTab {
   T alpha[3], c1[3], c2[3];
@@ -51,6 +67,21 @@ hipError_t launch_kick_table(const KickArgs& a, hipStream_t s)
   if (!a.tab) return hipErrorInvalidValue;
   hipLaunchKernelGGL((kick_table_kernel<T, NV>), dim3((unsigned)((a.np + 255) / 256)), dim3(256), 0, s, a);
   return hipGetLastError();
+}
+
+// nu_l < 0 in bit l
+__device__ __forceinline__ int kick_signs(const KickArgs& a, long long s)
+{
+  return (a.a[0][s] * a.scale[0] < 0.0 ? 1 : 0) | (a.a[1][s] * a.scale[1] < 0.0 ? 2 : 0) |
+         (a.a[2][s] * a.scale[2] < 0.0 ? 4 : 0);
+}
+
+template <typename T, int NV>
+__device__ __forceinline__ KickCoefs<T> kick_coefs(const KickArgs& a, long long s)
+{
+  const double nux = a.a[0][s] * a.scale[0], nuy = a.a[1][s] * a.scale[1], nuz = a.a[2][s] * a.scale[2];
+  const int l = threadIdx.x & 63;
+  return KickCoefs<T>{line_coef<T, NV>(fabs(l == 0 ? nux : (l == 1 ? nuy : nuz)), false)};
 }
 
 __device__ __forceinline__ bool tab_neg(int neg, int l) { return (neg >> l) & 1; }
@@ -98,21 +129,22 @@ __global__ __launch_bounds__((KickShape<T, NX, NY, NZ>::THREADS)) void kick_bloc
   const int tid = threadIdx.x;
   const long long s = blockIdx.x;
   const auto rs = buf_rsrc(static_cast<const T*>(a.f) + s * S::NV3, BLKB);
-  static_assert(NX == NY && NY == NZ, "the coefficient table is built for cubic blocks");
-  const KickTab<T>* __restrict__ tab = static_cast<const KickTab<T>*>(a.tab) + s;
-  const bool rx = tab_neg(tab->neg, 0), ry = tab_neg(tab->neg, 1), rz = tab_neg(tab->neg, 2);
-  const LineCoef<T> cx{tab->alpha[0], tab->c1[0], tab->c2[0], tab->shift[0], false};
-  const LineCoef<T> cy{tab->alpha[1], tab->c1[1], tab->c2[1], tab->shift[1], false};
-  const LineCoef<T> cz{tab->alpha[2], tab->c1[2], tab->c2[2], tab->shift[2], false};
+  static_assert(NX == NY && NY == NZ, "one line length for the three axes' coefficients");
+  const int neg = kick_signs(a, s);
+  const bool rx = tab_neg(neg, 0), ry = tab_neg(neg, 1), rz = tab_neg(neg, 2);
   // first vx sweep, lane (jy, jz): the line comes from HBM (a row of a wave is
   // 64 consecutive values) and goes to the lane's oriented (vy, vz) place
+  T v[NX];
+  if (tid < S::L0) {
+    const unsigned voff = (unsigned)tid * (unsigned)sizeof(T);
+#pragma unroll
+    for (int r = 0; r < NX; r++) v[r] = buf_load<T>(rs, voff, (unsigned)(rx ? NX - 1 - r : r) * ROWB);
+  }
+  const KickCoefs<T> kc = kick_coefs<T, NX>(a, s);
+  const LineCoef<T> cx = kc.axis(0), cy = kc.axis(1), cz = kc.axis(2);
   if (tid < S::L0) {
     const int jy = tid / NZ, jz = tid - jy * NZ;
     const int base = (ry ? NY - 1 - jy : jy) * S::SY + (rz ? NZ - 1 - jz : jz);
-    const unsigned voff = (unsigned)tid * (unsigned)sizeof(T);
-    T v[NX];
-#pragma unroll
-    for (int r = 0; r < NX; r++) v[r] = buf_load<T>(rs, voff, (unsigned)(rx ? NX - 1 - r : r) * ROWB);
     pfc_core<T, NX>(v, cx.alpha, cx.c1, cx.c2, false);
     store_shifted<T, NX>(v, cx.shift, false, [&](int r, T x) { L[base + r * S::SX] = x; });
   }
@@ -191,8 +223,6 @@ hipError_t launch_kick_cube(const KickArgs& a, hipStream_t s)
   static_assert(S::fits, "velocity block does not fit the LDS");
   static_assert(NV % Vec16<T>::n == 0, "16-byte output chunks stay inside a vz row");
   if (a.np <= 0) return hipSuccess;
-  const hipError_t e = launch_kick_table<T, NV>(a, s);
-  if (e != hipSuccess) return e;
   if (a.reps == 2)
     hipLaunchKernelGGL((kick_block<T, NV, NV, NV, 2>), dim3((unsigned)a.np), dim3(S::THREADS), 0, s, a);
   else

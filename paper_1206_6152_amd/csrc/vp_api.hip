@@ -83,8 +83,8 @@ struct vp_ctx {
   // per-velocity-cell line coefficients of the one-pass T_z T_y (null when
   // the grid has no such pass)
   void* dtab = nullptr;
-  // per-spatial-cell line coefficients of the kick passes (null when the
-  // velocity grid has none)
+  // per-spatial-cell line coefficients of the kick's slice and line passes
+  // (null when the velocity grid has none)
   void* ktab = nullptr;
   // phase timing (vp_profile_*): pending event pairs per phase
   bool profiling = false;
@@ -833,8 +833,7 @@ int vp_init(const vp_config* cfg, void* f_dev, void* hip_stream, vp_ctx** out)
   }
   {
     const int nv[3] = {cfg->nv[0], cfg->nv[1], cfg->nv[2]};
-    if ((vp::kick_fused_supported(cfg->dtype, nv) || vp::kick_lines_supported(cfg->dtype, nv) ||
-         vp::kick_planes_supported(cfg->dtype, nv)) &&
+    if ((vp::kick_lines_supported(cfg->dtype, nv) || vp::kick_planes_supported(cfg->dtype, nv)) &&
         (r = dalloc(&c->ktab, vp::kick_table_bytes(cfg->dtype, c->np), "kick coefficients"))) {
       release(c);
       return r;
