@@ -16,7 +16,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libvp.so")
 BUILD = os.path.join(ROOT, "_build")
-SOURCES = ["sweep.hip", "kick.hip", "drift.hip", "box_f32.hip", "box_f64.hip", "adjoint.hip", "kick_adjoint.hip", "gravity.hip", "vp_api.hip"]
+SOURCES = ["sweep.hip", "kick.hip", "drift.hip", "drift_pair_f32.hip", "drift_pair_f64.hip", "box_f32.hip", "box_f64.hip", "adjoint.hip", "kick_adjoint.hip", "gravity.hip", "vp_api.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950",

@@ -1,0 +1,31 @@
+// drift_pair_f32.hip -- the two-axis position passes of drift_pair.h in FP32, and
+// the entry of both types. gfx950.
+#include "drift_pair.h"
+
+namespace vp {
+namespace {
+
+bool has_length(int n)
+{
+  return n == 4 || n == 6 || n == 8 || n == 12 || n == 16 || n == 24 || n == 32 || n == 48 || n == 64;
+}
+
+}  // namespace
+
+bool drift_pair_supported(int na, int nb, long long nv3)
+{
+  return has_length(na) && has_length(nb) && na * nb <= 576 && nv3 % 256 == 0 && nv3 < (1LL << 31);
+}
+
+hipError_t launch_drift_pair_f32(const DriftPairArgs& p, int na, int nb, hipStream_t s)
+{
+  return launch_pair_t<float>(p, na, nb, s);
+}
+
+hipError_t launch_drift_pair(const DriftPairArgs& p, int dtype, int na, int nb, hipStream_t s)
+{
+  if (!drift_pair_supported(na, nb, p.nv3)) return hipErrorInvalidValue;
+  return dtype == 0 ? launch_drift_pair_f32(p, na, nb, s) : launch_drift_pair_f64(p, na, nb, s);
+}
+
+}  // namespace vp

@@ -86,6 +86,9 @@ struct vp_ctx {
   // per-spatial-cell line coefficients of the kick's slice and line passes
   // (null when the velocity grid has none)
   void* ktab = nullptr;
+  // position axes that share a pass of drift_pair: 1 for y and x, 2 for z and
+  // y, 0 for none
+  int pair = 0;
   // phase timing (vp_profile_*): pending event pairs per phase
   bool profiling = false;
   std::vector<hipEvent_t> ev_free;
@@ -655,15 +658,53 @@ int drift_yz(vp_ctx* c, double tau, const void* src, void* dst)
   return VP_OK;
 }
 
+// T_b T_a(tau) of two position axes in one pass (drift_pair_supported); with
+// sums (b = 0, a = 1) the pass leaves density sums (c->xsum)
+int drift_pair(vp_ctx* c, int a, int b, double tau, bool sums)
+{
+  const auto& k = c->cfg;
+  const int o = 3 - a - b;
+  const long long st[3] = {(long long)k.n[1] * k.n[2] * c->nv3, k.n[2] * c->nv3, c->nv3};
+  auto axis = [&](int l) {
+    vp::DriftPairAxis x{};
+    x.j_div = l == 0 ? (long long)k.nv[1] * k.nv[2] : (l == 1 ? k.nv[2] : 1);
+    x.j_mod = k.nv[l];
+    x.vmin = k.vmin[l];
+    x.dv = c->dv[l];
+    x.scale = tau / c->dx[l];
+    return x;
+  };
+  vp::DriftPairArgs q{};
+  q.f = c->f;
+  q.nv3 = c->nv3;
+  q.sa = st[a];
+  q.sb = st[b];
+  q.so = st[o];
+  q.nouter = k.n[o];
+  q.periodic = (k.bc == VP_BC_PERIODIC) ? 1 : 0;
+  q.a = axis(a);
+  q.b = axis(b);
+  q.part = sums ? c->xsum : nullptr;
+  PhaseScope scope(c, b == 0 ? 0 : 9);
+  LAUNCH(c, vp::launch_drift_pair(q, k.dtype, k.n[a], k.n[b], c->stream));
+  return VP_OK;
+}
+
 // T_x T_y T_z(tau): in one pass when the whole spatial grid fits on chip with a
-// chunk of velocity cells; else z and y in one pass when the (y, z) plane does.
+// chunk of velocity cells; else two axes in one pass when their plane does.
 // With sums the last pass leaves density sums (c->bsum, c->xsum).
 int drift(vp_ctx* c, double tau, bool x_sums = false)
 {
   int r;
   const auto& k = c->cfg;
   if (c->box3) return drift_box(c, tau, x_sums, c->f, nullptr);
-  if (vp::drift_yz_supported(k.dtype, k.n[1], k.n[2], c->nv3, k.nv[2])) {
+  if (c->pair == 1) {
+    if ((r = sweep(c, 2, tau))) return r;
+    return drift_pair(c, 1, 0, tau, x_sums);
+  }
+  if (c->pair == 2) {
+    if ((r = drift_pair(c, 2, 1, tau, false))) return r;
+  } else if (vp::drift_yz_supported(k.dtype, k.n[1], k.n[2], c->nv3, k.nv[2])) {
     if ((r = drift_yz(c, tau, c->f, nullptr))) return r;
   } else if ((r = sweep(c, 2, tau)) || (r = sweep(c, 1, tau))) {
     return r;
@@ -674,6 +715,29 @@ int drift(vp_ctx* c, double tau, bool x_sums = false)
   PhaseScope scope(c, 0);
   LAUNCH(c, vp::launch_sweep(a, c->cfg.dtype, c->stream));
   return VP_OK;
+}
+
+// Two position axes that share a pass (drift_pair) save one of the drift's
+// passes over f: 10 to 29 % of a step wherever the pass has more workgroups than
+// CUs (2 steps of 24 x 12 x 48 with 32^3 blocks FP32 6.41 -> 5.24 ms, 16 x 16 x
+// 64 7.91 -> 6.12, 48 x 48 x 12 with 24 x 24 x 32 FP64 18.7 -> 15.5); with fewer
+// its serial tiles show (8 x 48 x 4 with 16^3 FP64, 128 workgroups: 215 -> 255
+// us; 4 x 32 x 16, 256: 280 -> 288) and the single sweeps stay. Square planes with
+// a kernel of their own (drift_yz) keep it (16^3 x 16^3 FP32: 231 us, 251 with
+// the pair), except the FP32 64-cell plane, whose half-line chunks run at half
+// the copy rate (4 x 64 x 64 with 32^3: 7.36 -> 6.46 ms, with 16^3 the same).
+// Where both pairs will do, that of the smaller plane goes together (8 x 48 x 4
+// with 32^3 FP64: z and y 1.34 ms, y and x 1.47), or z and y where they are the
+// same, which leaves the sums to the x sweep.
+int pair_plan(const vp_ctx* c)
+{
+  const auto& k = c->cfg;
+  const long long chunks = c->nv3 / 256;
+  const bool yx = c->xsum && vp::drift_pair_supported(k.n[1], k.n[0], c->nv3) && k.n[2] * chunks > 256;
+  if (vp::drift_yz_supported(k.dtype, k.n[1], k.n[2], c->nv3, k.nv[2])) return yx && k.n[1] == 64 ? 1 : 0;
+  const bool zy = vp::drift_pair_supported(k.n[2], k.n[1], c->nv3) && k.n[0] * chunks > 256;
+  if (yx && zy) return k.n[0] < k.n[2] ? 1 : 2;
+  return yx ? 1 : (zy ? 2 : 0);
 }
 
 // drift, then the acceleration of the drifted f (one step's middle): the x
@@ -831,6 +895,7 @@ int vp_init(const vp_config* cfg, void* f_dev, void* hip_stream, vp_ctx** out)
       return r;
     }
   }
+  c->pair = c->box3 ? 0 : pair_plan(c);
   {
     const int nv[3] = {cfg->nv[0], cfg->nv[1], cfg->nv[2]};
     if ((vp::kick_lines_supported(cfg->dtype, nv) || vp::kick_planes_supported(cfg->dtype, nv)) &&
@@ -1132,12 +1197,14 @@ struct GradWork {
   void* user_f;
   double* user_accel;
   bool small;
-  explicit GradWork(vp_ctx* c_) : c(c_), user_f(c_->f), user_accel(c_->accel), small(c_->small) {}
+  int pair;
+  explicit GradWork(vp_ctx* c_) : c(c_), user_f(c_->f), user_accel(c_->accel), small(c_->small), pair(c_->pair) {}
   ~GradWork()
   {
     c->f = user_f;
     c->accel = user_accel;
     c->small = small;
+    c->pair = pair;
     for (void* p : bufs) hipFree(p);
     for (double* p : dbufs) hipFree(p);
   }
@@ -1237,10 +1304,13 @@ int grad_impl(vp_ctx* c, int nsteps, double dt, int k, void* lam, double* loss)
     g_err.clear();
   }
   auto A = [&](int n) { return ahist + (size_t)n * 3 * c->np; };
-  // FP32: the separate gravity kernels, whose roundings FP32 gradients have been
-  // differentiated with. A last bit of the acceleration can move the rounding of
+  // FP32: the separate gravity kernels and the x sweep's density sums, whose
+  // roundings FP32 gradients have been differentiated with. A last bit of the acceleration can move the rounding of
   // a line's alpha to FP32, and a corrector switch behind it.
-  if (c->cfg.dtype == VP_F32) c->small = false;
+  if (c->cfg.dtype == VP_F32) {
+    c->small = false;
+    c->pair = 0;
+  }
   const int nv[3] = {c->cfg.nv[0], c->cfg.nv[1], c->cfg.nv[2]};
   const bool fused_adj = vp::kick_adjoint_supported(c->cfg.dtype, nv);
 

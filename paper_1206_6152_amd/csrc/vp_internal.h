@@ -112,6 +112,26 @@ size_t drift_table_bytes(int dtype, long long nv3);
 bool drift_yz_supported(int dtype, int ny, int nz, long long nv3, long long nvz);
 hipError_t launch_drift_yz(const DriftArgs& a, int dtype, hipStream_t s);
 
+// Two position sweeps, along A and then B, in one pass over tiles of velocity
+// cells of the (A, B) plane at one index o of the third axis (drift_pair.hip).
+// With part (B = x, A = y, o = z) the pass leaves the density sums of the x
+// sweep's layout: part[((y nz + z) nv3/256 + chunk) nx + x].
+struct DriftPairAxis {
+  long long j_div, j_mod;        // velocity cell c moves with index (c / j_div) % j_mod
+  double vmin, dv, scale;        // scale = tau / dx
+};
+struct DriftPairArgs {
+  void* f;
+  long long nv3;
+  long long sa, sb, so;          // elements from one a, b, o to the next
+  int nouter;
+  int periodic;
+  DriftPairAxis a, b;
+  double* part;
+};
+bool drift_pair_supported(int na, int nb, long long nv3);
+hipError_t launch_drift_pair(const DriftPairArgs& a, int dtype, int na, int nb, hipStream_t s);
+
 // The half kick (or two) of a velocity block of any shape that fits the LDS, in
 // one pass (box.h).
 bool kick_box_supported(int dtype, const int nv[3]);
