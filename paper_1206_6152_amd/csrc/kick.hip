@@ -29,7 +29,7 @@ struct KickCoefs {
 };
 
 // The passes over larger blocks (kick_pair_block, kick_vxvy_pairs,
-// kick_lines_f64) do read a table: slices share a block, a workgroup alone on
+// kick_lines_f64, many FP32 32^3 blocks) do read a table: slices share a block, a workgroup alone on
 // its CU has little to hide the split behind, and against their passes the
 // launch is nothing (24^3 x 48^3 FP32: vz-slices 2.5 ms with the table, 3.1
 // without, vx-slices 2.43 and 2.55; a step of 32^3 x 32^3 FP64 0.3 % less with
@@ -84,6 +84,12 @@ __device__ __forceinline__ KickCoefs<T> kick_coefs(const KickArgs& a, long long 
   return KickCoefs<T>{line_coef<T, NV>(fabs(l == 0 ? nux : (l == 1 ? nuy : nuz)), false)};
 }
 
+template <typename T>
+__device__ __forceinline__ LineCoef<T> tab_axis(const KickTab<T>* __restrict__ t, int l)
+{
+  return LineCoef<T>{t->alpha[l], t->c1[l], t->c2[l], t->shift[l], false};
+}
+
 __device__ __forceinline__ bool tab_neg(int neg, int l) { return (neg >> l) & 1; }
 
 // ---- one-pass half kick -----------------------------------------------------
@@ -115,7 +121,7 @@ struct KickShape {
 // base, and the order in which the block is read back out. One code path
 // serves all eight sign combinations, which keeps the register footprint that
 // of a single line update.
-template <typename T, int NX, int NY, int NZ, int REPS>
+template <typename T, int NX, int NY, int NZ, int REPS, bool TAB>
 __global__ __launch_bounds__((KickShape<T, NX, NY, NZ>::THREADS)) void kick_block(KickArgs a)
 {
   using S = KickShape<T, NX, NY, NZ>;
@@ -130,7 +136,8 @@ __global__ __launch_bounds__((KickShape<T, NX, NY, NZ>::THREADS)) void kick_bloc
   const long long s = blockIdx.x;
   const auto rs = buf_rsrc(static_cast<const T*>(a.f) + s * S::NV3, BLKB);
   static_assert(NX == NY && NY == NZ, "one line length for the three axes' coefficients");
-  const int neg = kick_signs(a, s);
+  const KickTab<T>* __restrict__ tab = TAB ? static_cast<const KickTab<T>*>(a.tab) + s : nullptr;
+  const int neg = TAB ? tab->neg : kick_signs(a, s);
   const bool rx = tab_neg(neg, 0), ry = tab_neg(neg, 1), rz = tab_neg(neg, 2);
   // first vx sweep, lane (jy, jz): the line comes from HBM (a row of a wave is
   // 64 consecutive values) and goes to the lane's oriented (vy, vz) place
@@ -140,8 +147,13 @@ __global__ __launch_bounds__((KickShape<T, NX, NY, NZ>::THREADS)) void kick_bloc
 #pragma unroll
     for (int r = 0; r < NX; r++) v[r] = buf_load<T>(rs, voff, (unsigned)(rx ? NX - 1 - r : r) * ROWB);
   }
-  const KickCoefs<T> kc = kick_coefs<T, NX>(a, s);
-  const LineCoef<T> cx = kc.axis(0), cy = kc.axis(1), cz = kc.axis(2);
+  LineCoef<T> cx, cy, cz;
+  if constexpr (TAB) {
+    cx = tab_axis(tab, 0), cy = tab_axis(tab, 1), cz = tab_axis(tab, 2);
+  } else {
+    const KickCoefs<T> kc = kick_coefs<T, NX>(a, s);
+    cx = kc.axis(0), cy = kc.axis(1), cz = kc.axis(2);
+  }
   if (tid < S::L0) {
     const int jy = tid / NZ, jz = tid - jy * NZ;
     const int base = (ry ? NY - 1 - jy : jy) * S::SY + (rz ? NZ - 1 - jz : jz);
@@ -216,6 +228,14 @@ __global__ __launch_bounds__((KickShape<T, NX, NY, NZ>::THREADS)) void kick_bloc
   }
 }
 
+// blocks whose workgroup has a CU to itself (FP32 32^3): with a table on large
+// grids (kick_wants_table)
+template <typename T, int NV>
+constexpr bool kick_cube_alone()
+{
+  return KickShape<T, NV, NV, NV>::BYTES > 80 * 1024 && sizeof(T) == 4;
+}
+
 template <typename T, int NV>
 hipError_t launch_kick_cube(const KickArgs& a, hipStream_t s)
 {
@@ -223,10 +243,21 @@ hipError_t launch_kick_cube(const KickArgs& a, hipStream_t s)
   static_assert(S::fits, "velocity block does not fit the LDS");
   static_assert(NV % Vec16<T>::n == 0, "16-byte output chunks stay inside a vz row");
   if (a.np <= 0) return hipSuccess;
+  if constexpr (kick_cube_alone<T, NV>()) {
+    if (a.tab) {
+      const hipError_t e = launch_kick_table<T, NV>(a, s);
+      if (e != hipSuccess) return e;
+      if (a.reps == 2)
+        hipLaunchKernelGGL((kick_block<T, NV, NV, NV, 2, true>), dim3((unsigned)a.np), dim3(S::THREADS), 0, s, a);
+      else
+        hipLaunchKernelGGL((kick_block<T, NV, NV, NV, 1, true>), dim3((unsigned)a.np), dim3(S::THREADS), 0, s, a);
+      return hipGetLastError();
+    }
+  }
   if (a.reps == 2)
-    hipLaunchKernelGGL((kick_block<T, NV, NV, NV, 2>), dim3((unsigned)a.np), dim3(S::THREADS), 0, s, a);
+    hipLaunchKernelGGL((kick_block<T, NV, NV, NV, 2, false>), dim3((unsigned)a.np), dim3(S::THREADS), 0, s, a);
   else
-    hipLaunchKernelGGL((kick_block<T, NV, NV, NV, 1>), dim3((unsigned)a.np), dim3(S::THREADS), 0, s, a);
+    hipLaunchKernelGGL((kick_block<T, NV, NV, NV, 1, false>), dim3((unsigned)a.np), dim3(S::THREADS), 0, s, a);
   return hipGetLastError();
 }
 
@@ -731,6 +762,15 @@ bool kick_fused_supported(int dtype, const int nv[3])
 size_t kick_table_bytes(int dtype, long long np)
 {
   return (size_t)np * (dtype == 0 ? sizeof(KickTab<float>) : sizeof(KickTab<double>));
+}
+
+// The passes that read a table always, and FP32 32^3 cubes from 8192 blocks on:
+// there the split in every wave costs the two-kick pass 1.2 % (32 768 blocks:
+// 2.18 ms with the table, 2.21 without), its launch 4 us.
+bool kick_wants_table(int dtype, const int nv[3], long long np)
+{
+  if (kick_lines_supported(dtype, nv) || kick_planes_supported(dtype, nv)) return true;
+  return dtype == 0 && kick_fused_supported(dtype, nv) && nv[0] == 32 && np >= 8192;
 }
 
 bool kick_lines_supported(int dtype, const int nv[3])

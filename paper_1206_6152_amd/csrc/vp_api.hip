@@ -83,8 +83,8 @@ struct vp_ctx {
   // per-velocity-cell line coefficients of the one-pass T_z T_y (null when
   // the grid has no such pass)
   void* dtab = nullptr;
-  // per-spatial-cell line coefficients of the kick's slice and line passes
-  // (null when the velocity grid has none)
+  // per-spatial-cell line coefficients of the kick passes (null when they work
+  // them out themselves)
   void* ktab = nullptr;
   // position axes that share a pass of drift_pair: 1 for y and x, 2 for z and
   // y, 0 for none
@@ -898,7 +898,7 @@ int vp_init(const vp_config* cfg, void* f_dev, void* hip_stream, vp_ctx** out)
   c->pair = c->box3 ? 0 : pair_plan(c);
   {
     const int nv[3] = {cfg->nv[0], cfg->nv[1], cfg->nv[2]};
-    if ((vp::kick_lines_supported(cfg->dtype, nv) || vp::kick_planes_supported(cfg->dtype, nv)) &&
+    if (vp::kick_wants_table(cfg->dtype, nv, c->np) &&
         (r = dalloc(&c->ktab, vp::kick_table_bytes(cfg->dtype, c->np), "kick coefficients"))) {
       release(c);
       return r;

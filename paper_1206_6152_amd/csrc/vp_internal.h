@@ -60,14 +60,15 @@ struct KickArgs {
   double scale[3];
   int reps;   // 1: one half kick; 2: two consecutive half kicks with the same acceleration
   void* out;  // one-pass kick only: write the result here (same layout) instead of over f
-  // slice and line passes only: per-spatial-cell line coefficients of the
-  // three velocity sweeps, filled by the launch functions before the pass
-  // (kick_table_bytes(dtype, np) bytes)
+  // per-spatial-cell line coefficients of the three velocity sweeps, filled by
+  // the launch functions before the pass (kick_table_bytes(dtype, np) bytes);
+  // null where the kernels work them out (kick_wants_table)
   void* tab;
   int xcd_group;  // set by the launch functions: slices of one block on one XCD
 };
 
 size_t kick_table_bytes(int dtype, long long np);
+bool kick_wants_table(int dtype, const int nv[3], long long np);
 
 // True when a one-pass kernel exists for this velocity grid and element type.
 bool kick_fused_supported(int dtype, const int nv[3]);
