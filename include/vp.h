@@ -116,14 +116,12 @@ int vp_sweep(vp_ctx* ctx, int32_t axis, double tau);
 /* The two halves of Eq. (17). vp_kick: T_vz T_vy T_vx(tau) with the stored
  * acceleration (T_vx first). vp_drift: T_x T_y T_z(tau) (T_z first). Each is
  * exactly the corresponding vp_sweep calls in that order (same arithmetic, same
- * result bit for bit); vp_kick runs the three velocity sweeps of a spatial
- * cell in one pass over f when that cell's velocity block fits on chip
- * (cubic velocity grids: FP32 up to 32^3 and FP64 up to 24^3 in LDS, FP64
- * 32^3 in registers with one line per lane; 48^3 and 64^3 as a T_vx sweep
- * then T_vy T_vz in one pass over slices of whole (vy, vz) planes), and
- * vp_drift runs T_z and T_y in one pass when a (y, z) plane of a chunk of
- * velocity cells fits on chip (square planes of 16, 24, 32 or 48 cells, and
- * 64 in FP32), then T_x. */
+ * result bit for bit). vp_kick runs the three velocity sweeps of a spatial
+ * cell in one pass over f when that cell's velocity block fits on chip (in LDS,
+ * or FP64 32^3 in registers; 48^3 and 64^3 as a T_vx sweep then T_vy T_vz in
+ * one pass over slices of whole (vy, vz) planes). vp_drift runs two of the
+ * position sweeps in one pass when their plane fits on chip with a chunk of
+ * velocity cells, and all three where a small FP64 spatial grid does. */
 int vp_kick(vp_ctx* ctx, double tau);
 int vp_drift(vp_ctx* ctx, double tau);
 
@@ -174,7 +172,7 @@ int vp_dt(vp_ctx* ctx, double cfl, double* dt_host);
  * gravity solve (density, or the reduction of the T_x sums, Poisson,
  * acceleration), phase 7 the one-pass half
  * kick, phase 8 the one-pass pair of half kicks of vp_run, phase 9 the
- * one-pass T_y T_z, phase 10 the reverse sweeps and phase 11 the reverse
+ * one-pass T_y T_z or T_x T_y T_z (a one-pass T_x T_y counts as phase 0), phase 10 the reverse sweeps and phase 11 the reverse
  * gravity map of vp_grad and vp_*_adjoint, phase 12 a pass of two velocity
  * sweeps over slices of 48^3 or 64^3 velocity blocks (too large for one
  * pass), phase 13 the one-pass reverse half kick (vp_kick_adjoint, vp_grad).
