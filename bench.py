@@ -181,7 +181,7 @@ def kernel_name(phase, w, elem_bytes):
     if phase in ("kick", "kick2"):
         if elem_bytes == 8 and tuple(w.nv) == (32, 32, 32):
             return "vp::kick_lines_f64<%d>" % (2 if phase == "kick2" else 1)
-        table = elem_bytes == 4 and w.nv[0] == 32 and w.n[0] * w.n[1] * w.n[2] >= 8192
+        table = elem_bytes == 4 and w.nv[0] == 32 and w.n[0] * w.n[1] * w.n[2] >= 4096
         return "vp::kick_block<%s, %d, %d, %d, %d, %s>" % (t, w.nv[0], w.nv[1], w.nv[2], 2 if phase == "kick2" else 1,
                                                           "true" if table else "false")
     if phase == "kick_pair":

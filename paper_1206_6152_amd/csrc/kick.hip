@@ -764,13 +764,16 @@ size_t kick_table_bytes(int dtype, long long np)
   return (size_t)np * (dtype == 0 ? sizeof(KickTab<float>) : sizeof(KickTab<double>));
 }
 
-// The passes that read a table always, and FP32 32^3 cubes from 8192 blocks on:
-// there the split in every wave costs the two-kick pass 1.2 % (32 768 blocks:
-// 2.18 ms with the table, 2.21 without), its launch 4 us.
+// The passes that read a table always, and FP32 32^3 cubes from 4096 blocks on:
+// there the split in every wave costs the pass 1 to 2 % (a step with two kick
+// passes on 4096 blocks 4 us more without the table, on 32 768 14 us), its
+// launch less (on 1728 blocks 3 us a step). Smaller cubes share their CU: without
+// the table a kick of 24^3 blocks takes between 2 % more and 12 % less (FP32), of
+// 16^3 and 8^3 blocks 1 to 25 % less, at every size.
 bool kick_wants_table(int dtype, const int nv[3], long long np)
 {
   if (kick_lines_supported(dtype, nv) || kick_planes_supported(dtype, nv)) return true;
-  return dtype == 0 && kick_fused_supported(dtype, nv) && nv[0] == 32 && np >= 8192;
+  return dtype == 0 && kick_fused_supported(dtype, nv) && nv[0] == 32 && np >= 4096;
 }
 
 bool kick_lines_supported(int dtype, const int nv[3])
