@@ -70,8 +70,10 @@ __device__ __forceinline__ void adj_core(const T (&w)[N], T (&l)[N], T finf, con
     own = fma_(llp, p_mid ? T(-1) : T(2), own);
     own = fma_(llm, m_mid ? T(1) : T(-2), own);
     own = own + carry;
-    lfinf = fma_(llp, p_lo ? T(-2) : T(0), lfinf);
-    lfinf = fma_(llm, m_hi ? T(2) : T(0), lfinf);
+    // the factor that a bound switches is lam's, not the constant: a cell without
+    // its bound adds nothing, also where lam is infinite or not a number
+    lfinf = fma_(p_lo ? llp : T(0), T(-2), lfinf);
+    lfinf = fma_(m_hi ? llm : T(0), T(2), lfinf);
     // the two sums are kept up cell by cell: left to the compiler, both chains
     // move behind the loop, and every cell's operands live until then (24 FP32
     // cells: 168 registers and spills, 0.83 ms for the half kick's pass)
