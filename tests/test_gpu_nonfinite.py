@@ -1,6 +1,7 @@
 """Infinities and NaN go where the method sends them and no further: an adjoint
 that is not finite in one cell, against the cells that the oracle's reverse
-sweep reaches from it."""
+sweep reaches from it; and a state with infinite, NaN and nearly overflowing
+cells through the one-pass kick and drift, against the single sweeps."""
 import numpy as np
 import pytest
 
@@ -79,3 +80,35 @@ def test_one_pass_reverse_kick_of_a_non_finite_adjoint(dtype, nv):
     assert 1 <= int((~fine).sum()) <= 64
     assert torch.equal(torch.isfinite(lam_f), fine)
     assert torch.equal(lam_f[fine], lam_s[fine])
+
+
+@pytest.mark.parametrize("bad", [np.inf, -np.inf, np.nan, "max"])
+@pytest.mark.parametrize("dtype", [VP_F64, VP_F32])
+@pytest.mark.parametrize("bc", [VP_BC_PERIODIC, VP_BC_ISOLATED])
+@pytest.mark.parametrize("n,nv", [((4, 1, 1), (6, 3, 4)), ((1, 4, 1), (4, 4, 4)), ((1, 1, 4), (3, 3, 3)),
+                                  ((1, 1, 1), (12, 6, 8)), ((2, 3, 4), (8, 6, 4)), ((32, 1, 1), (64, 1, 1)),
+                                  ((6, 24, 4), (8, 16, 12))])
+def test_passes_of_a_non_finite_state(n, nv, bc, dtype, bad):
+    print("case", n, nv, bc, dtype, bad, flush=True)
+    import torch
+    w = small_workload(bc, n=n, nv=nv)
+    f0 = np.random.default_rng(8).uniform(0.5, 1.0, w.shape).astype(NP[dtype])
+    mid = tuple(s // 2 for s in w.shape)
+    f0[mid] = np.finfo(NP[dtype]).max if bad == "max" else bad
+    tau = 0.23
+    a = np.random.default_rng(5).uniform(-1, 1, (3,) + tuple(n)) * np.array([w.dv(l) for l in range(3)]).reshape(3, 1, 1, 1)
+    t = 0.9 * min(w.dx(l) / max(abs(w.vmin[l]), abs(w.vmax[l])) for l in range(3))
+
+    def bits(x):     # one pattern for every NaN
+        x = torch.where(torch.isnan(x), torch.full_like(x, float("nan")), x)
+        return x.view(torch.int64 if dtype == VP_F64 else torch.int32)
+    for one_pass, axes, tt in (("kick", (3, 4, 5), tau), ("drift", (2, 1, 0), t)):
+        f, g = _dev(f0), _dev(f0)
+        one, split = Simulator(config_of(w, dtype), f), Simulator(config_of(w, dtype), g)
+        for s in (one, split):
+            s.set_accel(_dev(a / tau))
+        getattr(one, one_pass)(tt)
+        for axis in axes:
+            split.sweep(axis, tt)
+        one.close(), split.close()
+        assert torch.equal(bits(f), bits(g)), one_pass
