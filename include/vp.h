@@ -237,8 +237,9 @@ double vp_cell_self_integral(double dx, double dy, double dz);
  * copies of f for the call (checkpoints, the states of one segment, and two
  * arrays in which each step's sweep inputs are regenerated from the step's
  * start), plus the acceleration of every step, and frees them before
- * returning (VP_ENOMEM if they do not fit). A third such array, which saves
- * three passes per step, is used where it fits too. Synchronises the stream. */
+ * returning (VP_ENOMEM, with f untouched, if they do not fit). A third such
+ * array, which saves three passes per step, is used where 1 GiB of device memory
+ * stays free beside it. Synchronises the stream. */
 int vp_sweep_adjoint(vp_ctx* ctx, int32_t axis, double tau, const void* f_in_dev, void* lam_dev,
                      double* lam_accel_dev);
 int vp_kick_adjoint(vp_ctx* ctx, double tau, const void* f_in_dev, void* lam_dev, double* lam_accel_dev);

@@ -437,6 +437,19 @@ bool x_sweep_sums(vp_ctx* c)
   return c->nv3 % 256 == 0 && vp::sweep_part_supported(a, c->cfg.dtype);
 }
 
+// room for one value per line of a sweep (c->dnu)
+int line_adjoints(vp_ctx* c, long long nlines)
+{
+  if (nlines <= c->dnu_len) return VP_OK;
+  hipFree(c->dnu);
+  c->dnu = nullptr;
+  c->dnu_len = 0;
+  int r = dalloc(&c->dnu, sizeof(double) * nlines, "line adjoints");
+  if (r) return r;
+  c->dnu_len = nlines;
+  return VP_OK;
+}
+
 // lam <- J^T lam of T_axis(tau) at forward input fin; velocity axes add the
 // acceleration adjoint to lam_a (if not null).
 int sweep_adjoint(vp_ctx* c, int axis, double tau, const void* fin, void* lam, double* lam_a,
@@ -456,14 +469,8 @@ int sweep_adjoint(vp_ctx* c, int axis, double tau, const void* fin, void* lam, d
     }
   }
   const bool want = axis >= 3 && lam_a;
-  if (want && a.nlines > c->dnu_len) {
-    hipFree(c->dnu);
-    c->dnu = nullptr;
-    c->dnu_len = 0;
-    int r = dalloc(&c->dnu, sizeof(double) * a.nlines, "line adjoints");
-    if (r) return r;
-    c->dnu_len = a.nlines;
-  }
+  int r;
+  if (want && (r = line_adjoints(c, a.nlines))) return r;
   PhaseScope scope(c, 10);
   LAUNCH(c, vp::launch_sweep_adjoint(a, c->cfg.dtype, fin, lam, want ? c->dnu : nullptr, c->stream));
   if (want) {
@@ -493,14 +500,22 @@ int kick_adjoint(vp_ctx* c, double tau, const void* fin, void* lam, double* lam_
   return VP_OK;
 }
 
-// c->radj = G^T D^T lam_a: transpose of potential -> acceleration, per spatial
-// cell (the density adjoint; lam then gains dv^3 times it)
-int density_adjoint(vp_ctx* c, const double* lam_a)
+// the fields of density_adjoint
+int density_adjoint_fields(vp_ctx* c)
 {
   const long long ext = (long long)(c->cfg.n[0] + 2) * (c->cfg.n[1] + 2) * (c->cfg.n[2] + 2);
   int r;
   if (!c->small && !c->lphi && (r = dalloc(&c->lphi, sizeof(double) * ext, "potential adjoint"))) return r;
   if (!c->radj && (r = dalloc(&c->radj, sizeof(double) * c->np, "density adjoint"))) return r;
+  return VP_OK;
+}
+
+// c->radj = G^T D^T lam_a: transpose of potential -> acceleration, per spatial
+// cell (the density adjoint; lam then gains dv^3 times it)
+int density_adjoint(vp_ctx* c, const double* lam_a)
+{
+  int r = density_adjoint_fields(c);
+  if (r) return r;
   PhaseScope scope(c, 11);
   if (c->small) {
     vp::SmallGravity q = c->sg;
@@ -1188,6 +1203,8 @@ int vp_accel_adjoint(vp_ctx* c, const double* lam_accel_dev, void* lam_dev)
 
 namespace {
 
+constexpr size_t kGradSpare = size_t(1) << 30;   // device memory that vp_grad's optional array leaves free
+
 struct GradWork {
   vp_ctx* c;
   std::vector<void*> bufs;
@@ -1299,11 +1316,6 @@ int grad_impl(vp_ctx* c, int nsteps, double dt, int k, void* lam, double* loss)
     if ((r = w.f(&st[i], fb))) return r;
   if ((r = w.f(&b1, fb)) || (r = w.f(&b2, fb))) return r;
   if ((r = w.d(&ahist, ab * (size_t)(nsteps + 1))) || (r = w.d(&lam_p, ab))) return r;
-  if (w.f(&b3, fb)) {
-    b3 = nullptr;
-    g_err.clear();
-  }
-  auto A = [&](int n) { return ahist + (size_t)n * 3 * c->np; };
   // FP32: the separate gravity kernels and the x sweep's density sums, whose
   // roundings FP32 gradients have been differentiated with. A last bit of the acceleration can move the rounding of
   // a line's alpha to FP32, and a corrector switch behind it.
@@ -1313,6 +1325,19 @@ int grad_impl(vp_ctx* c, int nsteps, double dt, int k, void* lam, double* loss)
   }
   const int nv[3] = {c->cfg.nv[0], c->cfg.nv[1], c->cfg.nv[2]};
   const bool fused_adj = vp::kick_adjoint_supported(c->cfg.dtype, nv);
+  // all that the reverse pass cannot do without, before f changes and before b3
+  const int vmin = std::min(nv[0], std::min(nv[1], nv[2]));
+  if ((r = density_adjoint_fields(c))) return r;
+  if (nsteps > 0 && !fused_adj && (r = line_adjoints(c, c->np * (c->nv3 / vmin)))) return r;
+  // b3 where the device has room for it and for what the runtime itself takes at
+  // a first launch (code objects, register spill space)
+  size_t dev_free = 0, dev_total = 0;
+  if (nsteps > 0 && hipMemGetInfo(&dev_free, &dev_total) != hipSuccess) hipGetLastError();
+  if (nsteps > 0 && dev_free >= fb + kGradSpare && w.f(&b3, fb)) {
+    b3 = nullptr;
+    g_err.clear();
+  }
+  auto A = [&](int n) { return ahist + (size_t)n * 3 * c->np; };
 
   // forward pass from f0, keeping checkpoints and every step's acceleration
   if ((r = copy_f(c, A(0), w.user_accel, ab))) return r;
