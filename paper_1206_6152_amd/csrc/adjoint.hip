@@ -36,7 +36,7 @@ namespace {
 // end, wrapped if periodic): where the line has a whole-cell shift, lam_g is
 // read straight into view order, each view cell from the storage cell that the
 // mirror and the transposed shift name.
-template <typename T, int N, typename AT, typename LA>
+template <typename T, int N, bool ALPHA, typename AT, typename LA>
 __device__ __forceinline__ double adj_line(const T* fin, T* lam, double nu, bool periodic, AT at, LA la)
 {
   const AdjCoef<T> k = adj_coef<T, N>(nu, periodic);
@@ -44,7 +44,7 @@ __device__ __forceinline__ double adj_line(const T* fin, T* lam, double nu, bool
   T w[N], l[N];
 #pragma unroll
   for (int r = 0; r < N; r++) w[r] = fin[at(r)];
-  if (k.shift == 0) {                         // storage order, then the mirror
+  auto straight = [&]() __attribute__((always_inline)) {   // storage order, then the mirror
 #pragma unroll
     for (int r = 0; r < N; r++) l[r] = la(r, lam[at(r)]);
 #pragma unroll
@@ -53,7 +53,17 @@ __device__ __forceinline__ double adj_line(const T* fin, T* lam, double nu, bool
       l[i] = neg ? q : p;
       l[N - 1 - i] = neg ? p : q;
     }
-  } else {
+  };
+  // Short FP32 lines are read before the branch on the shift (8 cells: 2 to 4 % of
+  // the pass), longer ones would hold their registers through it (24 cells: 6 to
+  // 11 % more).
+  constexpr bool EARLY = sizeof(T) == 4 && N <= 12;
+  if constexpr (EARLY) {
+    straight();
+#pragma unroll
+    for (int r = 0; r < N; r++) asm volatile("" : "+v"(l[r]));   // not sunk into the branch
+  }
+  if (k.shift != 0) {
     int m = k.shift;
     asm volatile("" : "+v"(m));               // the places below stay inside this rarely taken branch
 #pragma unroll
@@ -65,6 +75,8 @@ __device__ __forceinline__ double adj_line(const T* fin, T* lam, double nu, bool
       const T x = la(rs, lam[at(rs)]);
       l[i] = in ? x : T(0);
     }
+  } else if constexpr (!EARLY) {
+    straight();
   }
   // f_inf and the first storage cell that holds it (none on an empty line)
   T finf = T(0);
@@ -81,7 +93,7 @@ __device__ __forceinline__ double adj_line(const T* fin, T* lam, double nu, bool
     w[N - 1 - i] = neg ? x : y;
   }
   T lfinf, lalpha;
-  adj_core<T, N>(w, l, finf, k, periodic, lfinf, lalpha);
+  adj_core<T, N, ALPHA>(w, l, finf, k, periodic, lfinf, lalpha);
   // back to storage order
 #pragma unroll
   for (int i = 0; i < N / 2; i++) {
@@ -94,10 +106,10 @@ __device__ __forceinline__ double adj_line(const T* fin, T* lam, double nu, bool
   return neg ? -(double)lalpha : (double)lalpha;
 }
 
-template <typename T, int N, typename AT>
+template <typename T, int N, bool ALPHA, typename AT>
 __device__ __forceinline__ double adj_line(const T* fin, T* lam, double nu, bool periodic, AT at)
 {
-  return adj_line<T, N>(fin, lam, nu, periodic, at, [](int, T x) { return x; });
+  return adj_line<T, N, ALPHA>(fin, lam, nu, periodic, at, [](int, T x) { return x; });
 }
 
 __device__ __forceinline__ double adj_line_nu(const SweepArgs& a, long long o, long long c)
@@ -110,7 +122,9 @@ __device__ __forceinline__ double adj_line_nu(const SweepArgs& a, long long o, l
 // NARROW: the workgroup's first line is the uniform base and a lane's cells sit
 // at base + r*inner + off with a 32-bit offset (the host checks that they fit),
 // as in the forward strided sweep; otherwise 64-bit addressing per lane.
-template <typename T, int N, bool NARROW, bool ADD = false>
+// ALPHA: the lines' adjoints of nu are wanted (dnu). Position sweeps have no use
+// for them, and without them a line takes seven instructions per cell less.
+template <typename T, int N, bool ALPHA, bool NARROW, bool ADD = false>
 __global__ __launch_bounds__(256) void sweep_adj_kernel(SweepArgs a, const T* fin, T* lam, double* dnu)
 {
   const long long gid = (long long)blockIdx.x * 256 + threadIdx.x;
@@ -140,11 +154,11 @@ __global__ __launch_bounds__(256) void sweep_adj_kernel(SweepArgs a, const T* fi
     if constexpr (ADD) {
       const long long o = o0 + dov;
       const double* add = a.addend + c / (unsigned)a.add_div;
-      d = adj_line<T, N>(fin + b0, lam + b0, nu, a.periodic != 0,
+      d = adj_line<T, N, ALPHA>(fin + b0, lam + b0, nu, a.periodic != 0,
                          [&](int r) { return (long long)r * inner + off; },
                          [&](int r, T x) { return (T)((double)x + a.add_coef * add[(o * N + r) * a.add_stride]); });
     } else {
-      d = adj_line<T, N>(fin + b0, lam + b0, nu, a.periodic != 0,
+      d = adj_line<T, N, ALPHA>(fin + b0, lam + b0, nu, a.periodic != 0,
                          [&](int r) { return (long long)r * inner + off; });
     }
   } else {
@@ -152,10 +166,10 @@ __global__ __launch_bounds__(256) void sweep_adj_kernel(SweepArgs a, const T* fi
     const long long c = gid - o * a.inner;
     const long long base = o * (long long)N * a.inner + c;
     const long long inner = a.inner;
-    d = adj_line<T, N>(fin + base, lam + base, adj_line_nu(a, o, c), a.periodic != 0,
+    d = adj_line<T, N, ALPHA>(fin + base, lam + base, adj_line_nu(a, o, c), a.periodic != 0,
                        [&](int r) { return (long long)r * inner; });
   }
-  if (dnu) dnu[gid] = d;
+  if constexpr (ALPHA) dnu[gid] = d;
 }
 
 // Contiguous lines (inner == 1, the vz sweep): a workgroup stages LINES
@@ -169,7 +183,7 @@ struct AdjContig {
                                : (2 * 128 * P * (int)sizeof(T) <= 65536) ? 128 : 64;
 };
 
-template <typename T, int N>
+template <typename T, int N, bool ALPHA>
 __global__ __launch_bounds__((AdjContig<T, N>::LINES)) void sweep_adj_contig(SweepArgs a, const T* fin, T* lam,
                                                                              double* dnu)
 {
@@ -207,8 +221,8 @@ __global__ __launch_bounds__((AdjContig<T, N>::LINES)) void sweep_adj_contig(Swe
     const long long line = line0 + tid;
     const double nu = a.velocity ? a.accel[line / a.sp_div] * a.scale
                                  : (a.vmin + 0.5 * a.dv) * a.scale;   // one velocity cell on this axis
-    const double d = adj_line<T, N>(tf + tid * P, tl + tid * P, nu, a.periodic != 0, [&](int r) { return r; });
-    if (dnu) dnu[line] = d;
+    const double d = adj_line<T, N, ALPHA>(tf + tid * P, tl + tid * P, nu, a.periodic != 0, [&](int r) { return r; });
+    if constexpr (ALPHA) dnu[line] = d;
   }
   __syncthreads();
   if (nl == LINES) {
@@ -240,29 +254,34 @@ __global__ __launch_bounds__(256) void reduce_lines_kernel(double* lam_a, const 
   if (threadIdx.x == 0) lam_a[s] += scale * sh[0];
 }
 
+template <typename T, int N, bool ALPHA>
+hipError_t launch_adj_a(const SweepArgs& a, const T* fin, T* lam, double* dnu, hipStream_t s)
+{
+  if (a.inner == 1) {
+    if (a.addend) return hipErrorInvalidValue;
+    constexpr int LINES = AdjContig<T, N>::LINES;
+    hipLaunchKernelGGL((sweep_adj_contig<T, N, ALPHA>), dim3((unsigned)((a.nlines + LINES - 1) / LINES)), dim3(LINES),
+                       0, s, a, fin, lam, dnu);
+    return hipGetLastError();
+  }
+  const dim3 blocks((unsigned)((a.nlines + 255) / 256));
+  if (a.addend) {
+    if (!narrow_ok(a, N)) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((sweep_adj_kernel<T, N, ALPHA, true, true>), blocks, dim3(256), 0, s, a, fin, lam, dnu);
+  } else if (narrow_ok(a, N))
+    hipLaunchKernelGGL((sweep_adj_kernel<T, N, ALPHA, true>), blocks, dim3(256), 0, s, a, fin, lam, dnu);
+  else
+    hipLaunchKernelGGL((sweep_adj_kernel<T, N, ALPHA, false>), blocks, dim3(256), 0, s, a, fin, lam, dnu);
+  return hipGetLastError();
+}
+
 template <typename T, int N>
 hipError_t launch_adj_n(const SweepArgs& a, const void* fin, void* lam, double* dnu, hipStream_t s)
 {
   if (a.nlines <= 0) return hipSuccess;
-  if (a.inner == 1) {
-    if (a.addend) return hipErrorInvalidValue;
-    constexpr int LINES = AdjContig<T, N>::LINES;
-    hipLaunchKernelGGL((sweep_adj_contig<T, N>), dim3((unsigned)((a.nlines + LINES - 1) / LINES)), dim3(LINES), 0, s,
-                       a, static_cast<const T*>(fin), static_cast<T*>(lam), dnu);
-    return hipGetLastError();
-  }
-  const long long blocks = (a.nlines + 255) / 256;
-  if (a.addend) {
-    if (!narrow_ok(a, N)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((sweep_adj_kernel<T, N, true, true>), dim3((unsigned)blocks), dim3(256), 0, s, a,
-                       static_cast<const T*>(fin), static_cast<T*>(lam), dnu);
-  } else if (narrow_ok(a, N))
-    hipLaunchKernelGGL((sweep_adj_kernel<T, N, true>), dim3((unsigned)blocks), dim3(256), 0, s, a,
-                       static_cast<const T*>(fin), static_cast<T*>(lam), dnu);
-  else
-    hipLaunchKernelGGL((sweep_adj_kernel<T, N, false>), dim3((unsigned)blocks), dim3(256), 0, s, a,
-                       static_cast<const T*>(fin), static_cast<T*>(lam), dnu);
-  return hipGetLastError();
+  const T* f = static_cast<const T*>(fin);
+  T* l = static_cast<T*>(lam);
+  return dnu ? launch_adj_a<T, N, true>(a, f, l, dnu, s) : launch_adj_a<T, N, false>(a, f, l, dnu, s);
 }
 
 template <typename T>
