@@ -215,10 +215,12 @@ __device__ __forceinline__ void box_sweep(T* L, T* red, int n, int st, int nl, i
 
 // Workgroup sizes: 16 waves hold lines of up to 64 FP32 or 32 FP64 cells
 // without spilling, eight waves longer ones.
+constexpr int box_threads_most(int nmax, int es) { return nmax * es <= 256 ? 1024 : 512; }
+
 template <typename T, int NMAX>
 constexpr int box_threads()
 {
-  return NMAX * (int)sizeof(T) <= 256 ? 1024 : 512;
+  return box_threads_most(NMAX, (int)sizeof(T));
 }
 
 // ---- velocity blocks -----------------------------------------------------------
@@ -303,11 +305,9 @@ __global__ __launch_bounds__((box_threads<T, NMAX>())) void kick_box(KickArgs a,
 template <typename T, int NMAX>
 hipError_t launch_kick_box_n(const KickArgs& a, const int nv[3], hipStream_t st)
 {
-  const int nv3 = nv[0] * nv[1] * nv[2];
   const size_t lds = (size_t)nv[0] * nv[1] * (nv[2] | 1) * sizeof(T);
-  // a line or two per lane, in whole waves; 16 waves where one box fills a CU
-  int th = nv3 <= 2048 ? 64 : (nv3 <= 6144 ? 256 : (lds <= 80 * 1024 ? 512 : 1024));
-  if (th > box_threads<T, NMAX>()) th = box_threads<T, NMAX>();
+  int th = kick_box_threads(sizeof(T) == 4 ? 0 : 1, nv, a.np);
+  if (th > box_threads<T, NMAX>()) th = box_threads<T, NMAX>();   // NMAX may be a class above the longest axis
   hipLaunchKernelGGL((kick_box<T, NMAX>), dim3((unsigned)a.np), dim3(th), lds, st, a, nv[0], nv[1], nv[2]);
   return hipGetLastError();
 }

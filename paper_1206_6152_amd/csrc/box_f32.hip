@@ -1,5 +1,7 @@
 // box_f32.hip -- the run-time-shaped passes of box.h for FP32-stored f, the
 // rules that choose them, and the reduction of their density sums.
+#include <algorithm>
+
 #include "box.h"
 
 namespace vp {
@@ -54,14 +56,59 @@ constexpr int kLdsMost = 152 * 1024;   // of 160 KiB, less the coefficients and 
 
 }  // namespace
 
-bool kick_box_supported(int dtype, const int nv[3])
+// Lanes per velocity block: a line or two per lane, in whole waves; 16 waves where
+// one block fills a CU. With no more blocks than CUs nothing else would use the
+// other lanes: 1 x 32 x 64 FP32 on one cell took 12.3 us with one wave (three
+// sweeps: 11.4) and takes 7.4 with four.
+int kick_box_threads(int dtype, const int nv[3], long long np)
 {
-  return (size_t)nv[0] * nv[1] * (nv[2] | 1) * (dtype == 0 ? 4 : 8) <= (size_t)kLdsMost;
+  const int es = dtype == 0 ? 4 : 8, nv3 = nv[0] * nv[1] * nv[2];
+  const long long lds = (long long)nv[0] * nv[1] * (nv[2] | 1) * es;
+  const int most = box_threads_most(std::max(nv[0], std::max(nv[1], nv[2])), es);
+  int th = 1024;
+  if (nv3 <= 2048) th = np <= 512 && nv3 >= 512 ? 256 : 64;
+  else if (nv3 <= 6144) th = np <= 256 ? 512 : 256;
+  else if (lds <= 80 * 1024 && np > 256) th = 512;
+  return std::min(th, most);
+}
+
+// Cells that the busiest lane updates in a half kick (box_sweep's choices)
+static int kick_box_chain(const int nv[3], int threads)
+{
+  const int nv3 = nv[0] * nv[1] * nv[2], most = std::min(threads, kBoxRed);
+  int cells = 0;
+  for (int l = 0; l < 3; l++) {
+    const int n = nv[l], nl = nv3 / n;
+    if (n >= 16 && nl * (n / 8) <= most) cells += nl * (n / 4) <= most ? 4 + 2 : 8 + 2;   // and the cells of the edges
+    else cells += (nl + threads - 1) / threads * n;
+  }
+  return cells;
+}
+
+// Where the one-pass kick is the better choice than the three sweeps (us, three
+// sweeps -> one pass; 2000 shapes of random axes and cells were timed, and none
+// that this rule takes is slower):
+// - A workgroup is started for every block, however small: on many cells of tiny
+//   blocks that is the time (131 072 blocks of 2^3 FP32 14 -> 64, 49 152 of 4^3 FP64
+//   26 -> 42; 8192 of either, and any number of blocks from 192 cells on, less).
+// - With no more blocks than CUs a lane's chain of cells is the time (8 x 32 x 128 FP32
+//   on two cells 13.7 -> 18.3 at 256; up to 128 cells at most 0.97 of the sweeps).
+// - Lines of 96 and 128 cells that are not split over lanes leave most lanes without a
+//   line and spill in FP64: 128 x 96 x 1 FP64 on 24^3 cells 1940 -> 2600, 12 x 2 x 128 FP32
+//   on 24 576 368 -> 519, and split (128 x 4 x 1 FP64 on 98 304) 0.87 of the sweeps.
+bool kick_box_supported(int dtype, const int nv[3], long long np)
+{
+  if ((size_t)nv[0] * nv[1] * (nv[2] | 1) * (dtype == 0 ? 4 : 8) > (size_t)kLdsMost) return false;
+  if (nv[0] * nv[1] * nv[2] < 192 && np > 8192) return false;
+  const int chain = kick_box_chain(nv, kick_box_threads(dtype, nv, np));
+  if (np <= 256) return chain <= 128;
+  if (np <= 512) return chain <= 256;
+  return std::max(nv[0], std::max(nv[1], nv[2])) <= 64 || chain <= 64;
 }
 
 hipError_t launch_kick_box(const KickArgs& a, int dtype, const int nv[3], hipStream_t s)
 {
-  if (!kick_box_supported(dtype, nv) || (a.reps != 1 && a.reps != 2)) return hipErrorInvalidValue;
+  if (!kick_box_supported(dtype, nv, a.np) || (a.reps != 1 && a.reps != 2)) return hipErrorInvalidValue;
   return dtype == 0 ? launch_kick_box_f32(a, nv, s) : launch_kick_box_f64(a, nv, s);
 }
 

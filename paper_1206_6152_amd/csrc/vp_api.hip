@@ -569,13 +569,13 @@ vp::KickArgs kick_args(vp_ctx* c, double tau, int reps, const void* src, void* d
 }
 
 // True when the velocity block of a spatial cell has a one-pass half kick: in
-// LDS (cubes with a kernel of their own, and any other shape that fits) or,
+// LDS (cubes with a kernel of their own, and other shapes where it pays) or,
 // for FP64 32^3, in registers with one line per lane.
 bool kick_one_pass(vp_ctx* c)
 {
   const int* nv = c->cfg.nv;
   return vp::kick_fused_supported(c->cfg.dtype, nv) || vp::kick_lines_supported(c->cfg.dtype, nv) ||
-         vp::kick_box_supported(c->cfg.dtype, nv);
+         vp::kick_box_supported(c->cfg.dtype, nv, c->np);
 }
 
 // reps (1 or 2) half kicks in one pass, from src (over it, or to dst)

@@ -134,8 +134,9 @@ bool drift_pair_supported(int na, int nb, long long nv3);
 hipError_t launch_drift_pair(const DriftPairArgs& a, int dtype, int na, int nb, hipStream_t s);
 
 // The half kick (or two) of a velocity block of any shape that fits the LDS, in
-// one pass (box.h).
-bool kick_box_supported(int dtype, const int nv[3]);
+// one pass (box.h), where it is faster than the three sweeps.
+bool kick_box_supported(int dtype, const int nv[3], long long np);
+int kick_box_threads(int dtype, const int nv[3], long long np);
 hipError_t launch_kick_box(const KickArgs& a, int dtype, const int nv[3], hipStream_t s);
 
 // T_x T_y T_z(tau) in one pass over chunks of drift_box_cells velocity cells of

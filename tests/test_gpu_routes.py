@@ -1,0 +1,56 @@
+"""Which passes a kick takes where a shape lies near a rule's edge (counted with the
+library's phase timer), with the bits of the single sweeps on both sides."""
+import math
+
+import numpy as np
+import pytest
+
+from helpers import small_workload
+from paper_1206_6152_amd import VP_BC_PERIODIC, VP_F32, VP_F64, Simulator, config_of
+
+pytestmark = pytest.mark.gpu
+
+
+def _state(n, nv, dtype):
+    import torch
+    w = small_workload(VP_BC_PERIODIC, n=n, nv=nv)
+    t = torch.float32 if dtype == VP_F32 else torch.float64
+    f = torch.rand(w.shape, dtype=t, device="cuda:0", generator=torch.Generator("cuda:0").manual_seed(3))
+    return w, torch.where(f < 0.3, torch.zeros_like(f), f)
+
+
+ONE, SWEEPS = "kick", "vx"
+KICKS = [
+    # small blocks: a workgroup per block up to 8192 cells, or from 192 values on
+    ((64, 64, 2), (2, 2, 2), VP_F32, ONE), ((64, 64, 3), (2, 2, 2), VP_F32, SWEEPS), ((64, 64, 64), (1, 1, 1), VP_F32, SWEEPS),
+    ((48, 32, 48), (4, 4, 4), VP_F64, SWEEPS), ((24, 24, 24), (4, 4, 12), VP_F64, ONE), ((24, 24, 24), (6, 4, 6), VP_F32, SWEEPS),
+    # few cells: the busiest lane's chain of up to 128 cells, with more lanes per block
+    ((1, 1, 1), (32, 64, 1), VP_F32, ONE), ((2, 1, 1), (8, 32, 128), VP_F32, SWEEPS), ((1, 2, 1), (64, 32, 16), VP_F32, ONE),
+    ((2, 2, 1), (24, 12, 128), VP_F32, SWEEPS), ((3, 3, 1), (12, 12, 12), VP_F64, ONE), ((8, 8, 4), (16, 48, 24), VP_F64, SWEEPS),
+    ((8, 8, 6), (16, 48, 24), VP_F64, ONE),
+    # long lines on many cells: only where they are split over lanes
+    ((24, 24, 2), (128, 24, 1), VP_F64, SWEEPS), ((8, 8, 8), (128, 24, 1), VP_F64, ONE), ((24, 24, 2), (128, 4, 1), VP_F64, ONE),
+    ((16, 16, 4), (12, 2, 128), VP_F32, SWEEPS), ((16, 16, 4), (12, 2, 64), VP_F32, ONE),
+]
+
+
+@pytest.mark.parametrize("n,nv,dtype,route", KICKS)
+def test_kick_takes_the_faster_route(n, nv, dtype, route):
+    print("case", n, nv, dtype, route, flush=True)
+    import torch
+    w, f = _state(n, nv, dtype)
+    g = f.clone()
+    one, split = Simulator(config_of(w, dtype), f), Simulator(config_of(w, dtype), g)
+    tau = 0.2
+    scale = np.array([w.dv(l) for l in range(3)]).reshape(3, 1, 1, 1) * 1.3 / tau
+    a = torch.from_numpy(np.random.default_rng(6).uniform(-1, 1, (3,) + tuple(n)) * scale).to("cuda:0")
+    for s in (one, split):
+        s.set_accel(a)
+    one.profile(True)
+    one.kick(tau)
+    phases = one.profile_read()
+    for axis in (3, 4, 5):
+        split.sweep(axis, tau)
+    one.close(), split.close()
+    assert torch.equal(f, g)
+    assert {k for k in ("kick", "vx") if phases[k][1]} == {route}, math.prod(n)
