@@ -422,7 +422,7 @@ __global__ __launch_bounds__(THREADS) void gravity_small_kernel(SmallGravity q)
     if (q.part && q.xsums) {
       // the x sweep's sums, added as density_from_parts_kernel does: for each
       // cell the chunks k = g, g + G, ..., then the G group sums in order
-      const int n = n0, G = 256 / n, nchunk = (int)q.nchunk, nyz = n1 * n2;
+      const int n = n0, G = 256 / n, nchunk = (int)q.nchunk;
 #pragma unroll 1
       for (int s = t; s < np; s += THREADS) {
         const int q1 = div_small(s, n2, rn2), i2 = s - q1 * n2, x = div_small(q1, n1, rn1), yz = (q1 - x * n1) * n2 + i2;
@@ -1222,6 +1222,24 @@ void gravity_small_plan(SmallGravity& q)
   q.rg1 = 1.0f / (float)q.g.m[1];
   q.rn2 = 1.0f / (float)q.n.m[2];
   q.rn1 = 1.0f / (float)q.n.m[1];
+}
+
+// Whether the solve adds up the drift's sums (q.part) itself, which saves the
+// launch that would, some 3 to 5 us, or takes the density from that launch, whose
+// lanes are many more. One workgroup's lanes add the chunks of their cells one
+// after the other: box sums in groups, whose results one lane per cell adds up.
+// 500 grids were timed both ways, us a step with the sums in here against the
+// launch: x sums of up to 18 additions a lane (10 on more than 256 cells) between
+// 0.2 and 5.6 less; at 12 on 512 cells 0.5 more, at 32 (8^3 cells of 16) 1.4 more, at 96
+// (36 to 192 cells) up to 23 more, at 3456 (six cells) 330 more; box sums of up to 36
+// between 0.4 and 2.8 less, of 39 to 50 between 0.4 less and 1.4 more, of 256 (8^3 cells
+// of 128) 10 more.
+bool gravity_small_sums(const SmallGravity& q)
+{
+  const long long np = (long long)q.n.m[0] * q.n.m[1] * q.n.m[2], th = gravity_small_threads(q.g);
+  const long long rounds = (np + th - 1) / th;
+  if (q.xsums) return rounds * q.nchunk <= (np <= 256 ? 18 : 10);
+  return rounds * ((q.nchunk + q.groups - 1) / q.groups) + q.groups <= 36;
 }
 
 hipError_t launch_gravity_small(const SmallGravity& q, hipStream_t s)

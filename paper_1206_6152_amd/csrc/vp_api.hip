@@ -765,13 +765,11 @@ int drift_accel(vp_ctx* c, double tau)
     if (r) return r;
     PhaseScope scope(c, 6);
     const long long nchunk = (c->nv3 + c->box3 - 1) / c->box3;
-    // few sums: the one-workgroup solve adds them itself (512 KiB take it about
-    // the time of the launch that it saves)
-    if (c->small && c->np * nchunk <= 65536) {
-      vp::SmallGravity q = c->sg;
-      q.part = c->bsum;
-      q.nchunk = nchunk;
-      q.accel = c->accel;
+    vp::SmallGravity q = c->sg;
+    q.part = c->bsum;
+    q.nchunk = nchunk;
+    q.accel = c->accel;
+    if (c->small && vp::gravity_small_sums(q)) {
       LAUNCH(c, vp::launch_gravity_small(q, c->stream));
       return VP_OK;
     }
@@ -785,12 +783,12 @@ int drift_accel(vp_ctx* c, double tau)
   int r = drift(c, tau, /*x_sums=*/true);
   if (r) return r;
   PhaseScope scope(c, 6);
-  if (c->small && c->np * (c->nv3 / 256) <= 32768) {
-    vp::SmallGravity q = c->sg;
-    q.part = c->xsum;
-    q.xsums = 1;
-    q.nchunk = c->nv3 / 256;
-    q.accel = c->accel;
+  vp::SmallGravity q = c->sg;
+  q.part = c->xsum;
+  q.xsums = 1;
+  q.nchunk = c->nv3 / 256;
+  q.accel = c->accel;
+  if (c->small && vp::gravity_small_sums(q)) {
     LAUNCH(c, vp::launch_gravity_small(q, c->stream));
     return VP_OK;
   }

@@ -224,6 +224,8 @@ struct SmallGravity {
 };
 bool gravity_small_supported(Grid3 g);
 void gravity_small_plan(SmallGravity& q);
+// with part, nchunk and xsums set: whether the solve had better add the sums up itself
+bool gravity_small_sums(const SmallGravity& q);
 hipError_t launch_gravity_small(const SmallGravity& q, hipStream_t s);
 
 // data = rho (imag 0) on an n-grid (periodic) or zero-padded into the 2n-grid.

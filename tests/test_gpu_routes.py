@@ -1,5 +1,6 @@
-"""Which passes a kick takes where a shape lies near a rule's edge (counted with the
-library's phase timer), with the bits of the single sweeps on both sides."""
+"""Which passes a call takes where a shape lies near a rule's edge (counted or timed
+with the library's phase timer), with the results of the general path on both
+sides."""
 import math
 
 import numpy as np
@@ -54,3 +55,39 @@ def test_kick_takes_the_faster_route(n, nv, dtype, route):
     one.close(), split.close()
     assert torch.equal(f, g)
     assert {k for k in ("kick", "vx") if phases[k][1]} == {route}, math.prod(n)
+
+
+# few cells with many chunks of density sums each: both storage types, the x sweep's
+# and the one-pass drift's sums, on both sides of the rule
+SUMS = [((2, 2, 2), (96, 96, 96), VP_F32), ((12, 1, 2), (64, 48, 64), VP_F32), ((2, 2, 2), (12, 16, 24), VP_F32),
+        ((2, 2, 2), (16, 24, 24), VP_F32), ((16, 16, 2), (8, 16, 16), VP_F32), ((16, 16, 2), (8, 16, 24), VP_F32),
+        ((8, 8, 8), (8, 8, 8), VP_F64), ((4, 4, 1), (16, 16, 16), VP_F64), ((4, 4, 1), (16, 16, 24), VP_F64),
+        ((12, 12, 12), (1, 3, 8), VP_F64), ((2, 2, 2), (48, 64, 64), VP_F64)]
+
+
+@pytest.mark.parametrize("n,nv,dtype", SUMS)
+def test_density_sums_of_few_cells(n, nv, dtype):
+    print("case", n, nv, dtype, flush=True)
+    import torch
+    w, f = _state(n, nv, dtype)
+    h = f.clone()
+    t = 0.9 * min(w.dx(l) / max(abs(w.vmin[l]), abs(w.vmax[l])) for l in range(3))
+    zero = torch.zeros((3,) + tuple(n), dtype=torch.float64, device="cuda:0")
+    one, ref = Simulator(config_of(w, dtype), f), Simulator(config_of(w, dtype), h)
+    for s in (one, ref):
+        s.set_accel(zero)
+    one.step(t)
+    ref.drift(t)
+    ref.accel()
+    want, got = ref.get_accel(), one.get_accel()
+    # the same FP64 sums in another order: 2^21 terms of one sign at most
+    assert float((got - want).abs().max()) <= 1e-12 * float(want.abs().max())
+    # the gravity phase is a few launches: 5 to 30 us; one lane adding all of a
+    # cell's chunks took up to 330
+    best = 1e9
+    for _ in range(5):
+        one.profile(True)
+        one.step(t)
+        best = min(best, one.profile_read()["gravity"][0])
+    one.close(), ref.close()
+    assert best <= 0.08, best
