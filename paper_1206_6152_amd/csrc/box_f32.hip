@@ -22,7 +22,7 @@ hipError_t launch_drift_box_f32(const DriftBoxArgs& a, int w, hipStream_t s)
 }
 
 // rho[cell] = dv3 sum_k part[k np + cell]: a workgroup takes four cells (there
-// are few: up to 512), its 256 groups of lanes every 256th chunk with four sums
+// are few: drift_box_cells takes up to 512), its 256 groups of lanes every 256th chunk with four sums
 // in flight; the groups' sums are added in a tree. 64 cells of 6912 chunks took
 // 43 us with eight groups and 32 cells per workgroup.
 __global__ __launch_bounds__(1024) void box_density_kernel(double* rho, const double* part, int np, int nchunk,
@@ -116,13 +116,19 @@ hipError_t launch_kick_box(const KickArgs& a, int dtype, const int nv[3], hipStr
 // single sweeps (or the one-pass T_y T_z) are the better choice. The pass is
 // bound by vector issue (index decoding and run-time strides) and LDS latency,
 // so several workgroups have to share a CU: boxes of up to 40 KiB, with runs of
-// 128 bytes, or of 64 that share their lines with a neighbour on the same XCD.
-// Against the three sweeps, FP64: 4^3 x 24^3 10.8 us (16.6), 8^3 x 32^3 97 (121),
-// 6^3 x 48^3 144 (166); beyond 256 MiB it no longer pays (8^3 x 64^3, two steps:
-// 6.2 ms against 5.9), nor with longer axes (8 x 12 x 4 x 48^3 347
-// against 312, 64 x 4 x 4 x 12^3 37 against 33). Grids of under a MiB are bound by
-// latency alone (1D-1V 128 x 128: 6 us against three launches of 3 to 12); there
-// and in launches of at most 512 workgroups 32-byte runs and up to 80 KiB serve.
+// 128 bytes, or of 64 that share their lines with a neighbour on the same XCD; up
+// to 64 KiB where one or two workgroups per CU are all there are (8 x 8 x 6 x 4096
+// cells FP64, us a drift, three sweeps -> one pass: 22.5 -> 16.9, with half the run
+// 19.9; 8^3, 72 KiB, 22.2 -> 20.2, with half the run 18.0). FP64: 4^3 x 24^3 10.8 us
+// (16.6), 8^3 x 32^3 97 (121), 6^3 x 48^3 144 (166). The sweeps it is left to:
+// - beyond 256 MiB (8^3 x 64^3, two steps: 6.2 ms against 5.9), and longer axes from a
+//   MiB on (8 x 12 x 4 x 48^3 347 against 312, 64 x 4 x 4 x 12^3 37 against 33);
+// - more than 2304 workgroups of fewer than 48 cells each, whose start is the time
+//   (96^3 on one cell 18 -> 110, on 2^3 67 -> 167, on 2 x 3 x 6 the same);
+// - under a MiB, where latency is all (1D-1V 128 x 128: 6 us against three launches of
+//   3 to 12) and 32-byte runs and up to 80 KiB serve: long axes with more than 384
+//   cells, whose lines one or two workgroups take in turn (12^3 of one value 9.6 ->
+//   14.3, 3 x 6 x 128 of two 15.6 -> 32).
 //
 // FP64 only: the pass sums the density in another order than the x sweep, whose
 // sums FP32 gradients were differentiated with. A last bit of the acceleration
@@ -135,14 +141,15 @@ int drift_box_cells(int dtype, const int n[3], long long nv3)
   const int es = 8;
   const long long np = (long long)n[0] * n[1] * n[2];
   const long long bytes = np * nv3 * es;
-  if ((n[0] > 8 || n[1] > 8 || n[2] > 8) && bytes >= (1 << 20)) return 0;
+  if ((n[0] > 8 || n[1] > 8 || n[2] > 8) && (bytes >= (1 << 20) || np > 384)) return 0;
   if (bytes > (1 << 28)) return 0;
   for (int run = 128; run >= 32; run /= 2) {
     const int w = run / es;
     const size_t lds = box_lds(n[0], n[1], n[2], w, es);
     const long long blocks = (nv3 + w - 1) / w;
+    if (blocks > 2304 && np < 48) continue;
     if (lds <= 40 * 1024 && run >= 64 && blocks >= 256) return w;
-    if (lds <= 80 * 1024 && blocks <= 512 && (blocks >= 256 || run == 32)) return w;
+    if (lds <= (run == 32 ? 80 : 64) * 1024 && blocks <= 512 && (blocks >= 256 || run == 32)) return w;
   }
   return 0;
 }

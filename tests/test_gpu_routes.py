@@ -91,3 +91,30 @@ def test_density_sums_of_few_cells(n, nv, dtype):
         best = min(best, one.profile_read()["gravity"][0])
     one.close(), ref.close()
     assert best <= 0.08, best
+
+
+DRIFTS = [
+    # one pass counts as "drift_yz" (or as the sum's x sweep, "x", for a pair)
+    ((8, 8, 8), (16, 16, 16), ONE), ((8, 8, 6), (16, 16, 32), ONE), ((4, 4, 3), (32, 32, 48), ONE),
+    ((2, 2, 2), (24, 48, 32), ONE), ((2, 2, 2), (32, 32, 48), SWEEPS), ((1, 1, 1), (96, 96, 96), SWEEPS),
+    ((128, 1, 1), (128, 1, 1), ONE), ((6, 64, 1), (4, 4, 8), ONE), ((12, 12, 12), (1, 1, 1), SWEEPS),
+    ((48, 48, 1), (4, 4, 3), SWEEPS), ((3, 6, 128), (2, 1, 1), SWEEPS),
+]
+
+
+@pytest.mark.parametrize("n,nv,route", DRIFTS)
+def test_fp64_drift_takes_the_faster_route(n, nv, route):
+    print("case", n, nv, route, flush=True)
+    import torch
+    w, f = _state(n, nv, VP_F64)
+    g = f.clone()
+    one, split = Simulator(config_of(w, VP_F64), f), Simulator(config_of(w, VP_F64), g)
+    t = 1.3 * min(w.dx(l) / max(abs(w.vmin[l]), abs(w.vmax[l])) for l in range(3))
+    one.profile(True)
+    one.drift(t)
+    phases = one.profile_read()
+    for axis in (2, 1, 0):
+        split.sweep(axis, t)
+    one.close(), split.close()
+    assert torch.equal(f, g)
+    assert (phases["drift_yz"][1] == 1 and phases["x"][1] == 0) == (route == ONE), phases
