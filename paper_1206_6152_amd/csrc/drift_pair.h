@@ -43,7 +43,12 @@ struct PairShape {
   static constexpr int KA = (NB + S - 1) / S, KB = (NA + S - 1) / S;   // lines per lane
   // waves per SIMD: what the registers of one set of lines and the LDS allow
   static constexpr int LIVE = (KA * NA > KB * NB ? KA * NA : KB * NB) * (int)sizeof(T) / 4;
-  static constexpr int REGW = 512 / (LIVE + 64), LDSW = 160 * 1024 / BYTES * THREADS / 256;
+  // and what a wave needs beside them (measured): FP64 temporaries, and the more of
+  // them the more lines a lane holds
+  static constexpr bool EVEN = NA % S == 0 && NB % S == 0;
+  static constexpr int TEMPS =
+      sizeof(T) == 8 ? (KA * KB > 1 ? 64 + 3 * LIVE / 4 : 72) : (LIVE >= 32 && !EVEN ? 88 : 64);
+  static constexpr int REGW = 512 / (LIVE + TEMPS), LDSW = 160 * 1024 / BYTES * THREADS / 256;
   static constexpr int WAVES = REGW < LDSW ? REGW : LDSW;
   static constexpr int LEAST = (THREADS + 255) / 256;                  // one workgroup
   static constexpr int WPE = WAVES < LEAST ? LEAST : (WAVES > 8 ? 8 : WAVES);
@@ -217,15 +222,21 @@ hipError_t launch_pair(const DriftPairArgs& p, hipStream_t s)
   return hipGetLastError();
 }
 
-// the planes with a kernel: up to 576 cells (two tiles of 128-byte runs on a
-// CU) of two of these lengths
+// The planes with a kernel: up to 576 cells (two tiles of 128-byte runs on a
+// CU) of two of these lengths, but FP64 of 6 and 64, where a lane's lines leave room
+// for one wave on a SIMD (384 to 1152 workgroups: 0.9 to 1.4 times the two sweeps).
+constexpr bool pair_plane(int es, int na, int nb)
+{
+  return na * nb <= 576 && !(es == 8 && na * nb == 384 && (na == 64 || nb == 64));
+}
+
 template <typename T, int NA>
 hipError_t launch_a(const DriftPairArgs& p, int nb, hipStream_t s)
 {
   switch (nb) {
 #define CASE(N) \
   case N: \
-    if constexpr (NA * N <= 576) return launch_pair<T, NA, N>(p, s); \
+    if constexpr (pair_plane(sizeof(T), NA, N)) return launch_pair<T, NA, N>(p, s); \
     break;
     CASE(4) CASE(6) CASE(8) CASE(12) CASE(16) CASE(24) CASE(32) CASE(48) CASE(64)
 #undef CASE

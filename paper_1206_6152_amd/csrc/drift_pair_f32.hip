@@ -12,9 +12,10 @@ bool has_length(int n)
 
 }  // namespace
 
-bool drift_pair_supported(int na, int nb, long long nv3)
+bool drift_pair_supported(int dtype, int na, int nb, long long nv3)
 {
-  return has_length(na) && has_length(nb) && na * nb <= 576 && nv3 % 256 == 0 && nv3 < (1LL << 31);
+  return has_length(na) && has_length(nb) && pair_plane(dtype == 0 ? 4 : 8, na, nb) && nv3 % 256 == 0 &&
+         nv3 < (1LL << 31);
 }
 
 hipError_t launch_drift_pair_f32(const DriftPairArgs& p, int na, int nb, hipStream_t s)
@@ -24,7 +25,7 @@ hipError_t launch_drift_pair_f32(const DriftPairArgs& p, int na, int nb, hipStre
 
 hipError_t launch_drift_pair(const DriftPairArgs& p, int dtype, int na, int nb, hipStream_t s)
 {
-  if (!drift_pair_supported(na, nb, p.nv3)) return hipErrorInvalidValue;
+  if (!drift_pair_supported(dtype, na, nb, p.nv3)) return hipErrorInvalidValue;
   return dtype == 0 ? launch_drift_pair_f32(p, na, nb, s) : launch_drift_pair_f64(p, na, nb, s);
 }
 

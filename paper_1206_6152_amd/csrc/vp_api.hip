@@ -733,11 +733,13 @@ int drift(vp_ctx* c, double tau, bool x_sums = false)
 }
 
 // Two position axes that share a pass (drift_pair) save one of the drift's
-// passes over f: 10 to 29 % of a step wherever the pass has more workgroups than
-// CUs (2 steps of 24 x 12 x 48 with 32^3 blocks FP32 6.41 -> 5.24 ms, 16 x 16 x
-// 64 7.91 -> 6.12, 48 x 48 x 12 with 24 x 24 x 32 FP64 18.7 -> 15.5); with fewer
-// its serial tiles show (8 x 48 x 4 with 16^3 FP64, 128 workgroups: 215 -> 255
-// us; 4 x 32 x 16, 256: 280 -> 288) and the single sweeps stay. Square planes with
+// passes over f: 10 to 29 % of a step wherever the pass has enough workgroups
+// (2 steps of 24 x 12 x 48 with 32^3 blocks FP32 6.41 -> 5.24 ms, 16 x 16 x 64 7.91 ->
+// 6.12, 48 x 48 x 12 with 24 x 24 x 32 FP64 18.7 -> 15.5). With few its serial tiles
+// show, and the single sweeps stay (2600 shapes of up to 2500 workgroups, drift
+// against the sweeps): up to 400 workgroups between 0.7 and 1.36 of their time, and
+// up to 600 as much as 1.17 for planes over 320 cells, whose tiles have half the
+// rows; of what the rule takes, 0.51 to 1.08, 0.82 on average. Square planes with
 // a kernel of their own (drift_yz) keep it (16^3 x 16^3 FP32: 231 us, 251 with
 // the pair), except the FP32 64-cell plane, whose half-line chunks run at half
 // the copy rate (4 x 64 x 64 with 32^3: 7.36 -> 6.46 ms, with 16^3 the same).
@@ -748,9 +750,13 @@ int pair_plan(const vp_ctx* c)
 {
   const auto& k = c->cfg;
   const long long chunks = c->nv3 / 256;
-  const bool yx = c->xsum && vp::drift_pair_supported(k.n[1], k.n[0], c->nv3) && k.n[2] * chunks > 256;
+  auto pays = [&](int a, int b, int o) {
+    return vp::drift_pair_supported(k.dtype, k.n[a], k.n[b], c->nv3) &&
+           k.n[o] * chunks > (k.n[a] * k.n[b] > 320 ? 600 : 400);
+  };
+  const bool yx = c->xsum && pays(1, 0, 2);
   if (vp::drift_yz_supported(k.dtype, k.n[1], k.n[2], c->nv3, k.nv[2])) return yx && k.n[1] == 64 ? 1 : 0;
-  const bool zy = vp::drift_pair_supported(k.n[2], k.n[1], c->nv3) && k.n[0] * chunks > 256;
+  const bool zy = pays(2, 1, 0);
   if (yx && zy) return k.n[0] < k.n[2] ? 1 : 2;
   return yx ? 1 : (zy ? 2 : 0);
 }

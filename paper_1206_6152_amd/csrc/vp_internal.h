@@ -130,7 +130,7 @@ struct DriftPairArgs {
   DriftPairAxis a, b;
   double* part;
 };
-bool drift_pair_supported(int na, int nb, long long nv3);
+bool drift_pair_supported(int dtype, int na, int nb, long long nv3);
 hipError_t launch_drift_pair(const DriftPairArgs& a, int dtype, int na, int nb, hipStream_t s);
 
 // The half kick (or two) of a velocity block of any shape that fits the LDS, in

@@ -7,14 +7,14 @@ import numpy as np
 import pytest
 
 from helpers import small_workload
-from paper_1206_6152_amd import VP_BC_PERIODIC, VP_F32, VP_F64, Simulator, config_of
+from paper_1206_6152_amd import VP_BC_ISOLATED, VP_BC_PERIODIC, VP_F32, VP_F64, Simulator, config_of
 
 pytestmark = pytest.mark.gpu
 
 
-def _state(n, nv, dtype):
+def _state(n, nv, dtype, bc=VP_BC_PERIODIC):
     import torch
-    w = small_workload(VP_BC_PERIODIC, n=n, nv=nv)
+    w = small_workload(bc, n=n, nv=nv)
     t = torch.float32 if dtype == VP_F32 else torch.float64
     f = torch.rand(w.shape, dtype=t, device="cuda:0", generator=torch.Generator("cuda:0").manual_seed(3))
     return w, torch.where(f < 0.3, torch.zeros_like(f), f)
@@ -118,3 +118,45 @@ def test_fp64_drift_takes_the_faster_route(n, nv, route):
     one.close(), split.close()
     assert torch.equal(f, g)
     assert (phases["drift_yz"][1] == 1 and phases["x"][1] == 0) == (route == ONE), phases
+
+
+# two position axes in one pass: "yx", "zy", or the single sweeps ("-"), for both types
+PAIRS = [
+    ((6, 4, 48), (16, 16, 16), "yx", "yx"), ((6, 4, 48), (16, 8, 16), "-", "-"), ((12, 16, 24), (16, 24, 12), "yx", "yx"),
+    ((4, 64, 64), (8, 16, 16), "yx", "yx"), ((6, 64, 48), (24, 24, 8), "yx", "-"), ((12, 48, 16), (24, 24, 24), "yx", "yx"),
+    ((12, 48, 16), (16, 24, 24), "-", "-"), ((8, 12, 24), (12, 12, 32), "yx", "yx"),
+    ((48, 6, 4), (8, 32, 12), "zy", "zy"), ((24, 24, 4), (16, 24, 16), "zy", "zy"), ((48, 8, 48), (16, 16, 16), "zy", "zy"),
+    ((24, 24, 16), (16, 32, 16), "zy", "zy"), ((24, 24, 16), (16, 24, 16), "-", "-"), ((48, 12, 8), (8, 32, 12), "zy", "zy"),
+    ((48, 64, 6), (8, 32, 16), "zy", "-"),
+]
+
+
+@pytest.mark.parametrize("bc,mag", [(VP_BC_PERIODIC, 0.9), (VP_BC_PERIODIC, 2.3), (VP_BC_ISOLATED, 2.3)])
+@pytest.mark.parametrize("dtype", [VP_F32, VP_F64])
+@pytest.mark.parametrize("n,nv,r32,r64", PAIRS)
+def test_drift_pairs_take_the_faster_route(n, nv, r32, r64, dtype, bc, mag):
+    print("case", n, nv, dtype, bc, mag, flush=True)
+    import torch
+    w, f = _state(n, nv, dtype, bc)
+    g = f.clone()
+    one, split = Simulator(config_of(w, dtype), f), Simulator(config_of(w, dtype), g)
+    tau = mag * min(w.dx(l) / max(abs(w.vmin[l]), abs(w.vmax[l])) for l in range(3))
+    for tt in (tau, -tau):
+        one.profile(True)
+        one.drift(tt)
+        p = {k: v[1] for k, v in one.profile_read().items()}
+        for axis in (2, 1, 0):
+            split.sweep(axis, tt)
+        assert torch.equal(f, g)
+        took = "zy" if p["drift_yz"] and not p["z"] else ("-" if p["y"] else "yx")
+        assert took == (r32 if dtype == VP_F32 else r64), p
+    zero = torch.zeros((3,) + tuple(n), dtype=torch.float64, device="cuda:0")
+    one.set_accel(zero)
+    one.step(tau)
+    for axis in (2, 1, 0):
+        split.sweep(axis, tau)
+    split.accel()
+    want, got = split.get_accel(), one.get_accel()
+    one.close(), split.close()
+    # the same FP64 sums in another order
+    assert float((got - want).abs().max()) <= 1e-12 * float(want.abs().max())
