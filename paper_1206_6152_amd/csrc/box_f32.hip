@@ -95,7 +95,8 @@ static int kick_box_chain(const int nv[3], int threads)
 //   on two cells 13.7 -> 18.3 at 256; up to 128 cells at most 0.97 of the sweeps).
 // - Lines of 96 and 128 cells that are not split over lanes leave most lanes without a
 //   line and spill in FP64: 128 x 96 x 1 FP64 on 24^3 cells 1940 -> 2600, 12 x 2 x 128 FP32
-//   on 24 576 368 -> 519, and split (128 x 4 x 1 FP64 on 98 304) 0.87 of the sweeps.
+//   on 24 576 368 -> 519; split ones take half of the sweeps' time on few cells, but the
+//   kernel's registers hold eight blocks on a CU: 1 x 96 x 3 FP32 on 262 144 668 -> 859.
 bool kick_box_supported(int dtype, const int nv[3], long long np)
 {
   if ((size_t)nv[0] * nv[1] * (nv[2] | 1) * (dtype == 0 ? 4 : 8) > (size_t)kLdsMost) return false;
@@ -103,7 +104,7 @@ bool kick_box_supported(int dtype, const int nv[3], long long np)
   const int chain = kick_box_chain(nv, kick_box_threads(dtype, nv, np));
   if (np <= 256) return chain <= 128;
   if (np <= 512) return chain <= 256;
-  return std::max(nv[0], std::max(nv[1], nv[2])) <= 64 || chain <= 64;
+  return std::max(nv[0], std::max(nv[1], nv[2])) <= 64 || (chain <= 64 && np <= 16384);
 }
 
 hipError_t launch_kick_box(const KickArgs& a, int dtype, const int nv[3], hipStream_t s)

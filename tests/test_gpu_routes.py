@@ -32,6 +32,7 @@ KICKS = [
     # long lines on many cells: only where they are split over lanes
     ((24, 24, 2), (128, 24, 1), VP_F64, SWEEPS), ((8, 8, 8), (128, 24, 1), VP_F64, ONE), ((24, 24, 2), (128, 4, 1), VP_F64, ONE),
     ((16, 16, 4), (12, 2, 128), VP_F32, SWEEPS), ((16, 16, 4), (12, 2, 64), VP_F32, ONE),
+    ((64, 64, 8), (1, 96, 3), VP_F32, SWEEPS), ((64, 64, 4), (1, 96, 3), VP_F32, ONE),
 ]
 
 
