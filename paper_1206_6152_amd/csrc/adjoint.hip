@@ -254,6 +254,17 @@ __global__ __launch_bounds__(256) void reduce_lines_kernel(double* lam_a, const 
   if (threadIdx.x == 0) lam_a[s] += scale * sh[0];
 }
 
+// LDS that a workgroup of a strided FP32 velocity sweep asks for without using it,
+// so that only two share a CU: on arrays beyond the last-level cache the long lines
+// of two arrays, read and written by every wave that the registers allow, cost more
+// than the waves hide (vx lines of 24 cells, 1.7 GB, us: seven workgroups on a CU
+// 1088, two 964; without alpha's adjoint 1029 and 914; 32 cells, 0.8 GB, 482 and 426).
+// Smaller arrays, shorter lines and position sweeps lose up to 14 % by it.
+static unsigned adj_spare_lds(const SweepArgs& a, int es)
+{
+  return a.velocity && es == 4 && a.n >= 24 && a.nlines * a.n * es >= (1LL << 28) ? 79 * 1024 : 0;
+}
+
 template <typename T, int N, bool ALPHA>
 hipError_t launch_adj_a(const SweepArgs& a, const T* fin, T* lam, double* dnu, hipStream_t s)
 {
@@ -265,13 +276,14 @@ hipError_t launch_adj_a(const SweepArgs& a, const T* fin, T* lam, double* dnu, h
     return hipGetLastError();
   }
   const dim3 blocks((unsigned)((a.nlines + 255) / 256));
+  const unsigned spare = adj_spare_lds(a, (int)sizeof(T));
   if (a.addend) {
     if (!narrow_ok(a, N)) return hipErrorInvalidValue;
     hipLaunchKernelGGL((sweep_adj_kernel<T, N, ALPHA, true, true>), blocks, dim3(256), 0, s, a, fin, lam, dnu);
   } else if (narrow_ok(a, N))
-    hipLaunchKernelGGL((sweep_adj_kernel<T, N, ALPHA, true>), blocks, dim3(256), 0, s, a, fin, lam, dnu);
+    hipLaunchKernelGGL((sweep_adj_kernel<T, N, ALPHA, true>), blocks, dim3(256), spare, s, a, fin, lam, dnu);
   else
-    hipLaunchKernelGGL((sweep_adj_kernel<T, N, ALPHA, false>), blocks, dim3(256), 0, s, a, fin, lam, dnu);
+    hipLaunchKernelGGL((sweep_adj_kernel<T, N, ALPHA, false>), blocks, dim3(256), spare, s, a, fin, lam, dnu);
   return hipGetLastError();
 }
 
