@@ -231,8 +231,13 @@ double vp_cell_self_integral(double dx, double dy, double dz);
  * recomputes one segment at a time; writes dL/df0 to grad_f0_dev (device,
  * layout and type of f, caller-owned, 16-byte aligned) and L to *loss_host.
  * On return f holds the final state and the context its acceleration, as after
- * vp_run(nsteps, dt) (VP_F32 on small spatial grids: up to the FP64 rounding of
- * the gravity solve, which takes the same route at every grid size here).
+ * vp_run(nsteps, dt): in VP_F64 bit for bit. In VP_F32 the steps sum the density
+ * and solve for the acceleration by the same launches on every grid, where vp_run
+ * has one launch for small spatial grids (a transform grid of up to 4608 cells) and
+ * other sums in its one-pass T_x T_y. There the accelerations differ by the
+ * rounding of FP64 sums; where that moves the FP32 rounding of a sweep's
+ * coefficients, f differs by FP32 rounding. The first half kick uses the context's
+ * acceleration as it stands, like vp_run.
  * Allocates ceil(nsteps/ckpt_every) + ckpt_every + 1
  * copies of f for the call (checkpoints, the states of one segment, and two
  * arrays in which each step's sweep inputs are regenerated from the step's
