@@ -8,7 +8,7 @@
 //              or twice) for blocks that fit the LDS and have no kernel of
 //              their own (kick.hip has cubes of 8, 16, 24, 32)
 //   drift_box  W consecutive velocity cells of a whole spatial grid: T_z, T_y,
-//              T_x, with the density sums of the new f
+//              T_x, with the density sums of the new f (FP64)
 //
 // A line's length has to be a constant where the line is held in registers, so
 // a sweep branches once (uniformly) to the code of its length; a kernel is
@@ -349,6 +349,7 @@ template <typename T, int NMAX>
 __global__ __launch_bounds__((box_threads<T, NMAX>())) void drift_box(const T* fin, T* fout, DriftBoxShape s,
                                                                       double* part)
 {
+  static_assert(sizeof(T) == 8, "drift_box_cells offers FP64 only");
   extern __shared__ __attribute__((aligned(16))) char lds_raw[];
   T* L = reinterpret_cast<T*>(lds_raw);
   __shared__ BoxCoef<T> cf[3][kBoxW];
@@ -404,7 +405,7 @@ __global__ __launch_bounds__((box_threads<T, NMAX>())) void drift_box(const T* f
   // difference of the two fluxes is not zero.
   const bool ones = periodic && (n0 == 1 || n1 == 1 || n2 == 1);
   bool huge = false;
-  auto look = [&](T v) { huge = huge || !(fabs(v) < (sizeof(T) == 4 ? T(0x1p110) : T(0x1p1000))); };
+  auto look = [&](T v) { huge = huge || !(fabs(v) < T(0x1p1000)); };
   for (int e0 = tid; e0 < nvec; e0 += 4 * nth) {
 #pragma unroll
     for (int k = 0; k < 4; k++) {

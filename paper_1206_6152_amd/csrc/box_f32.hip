@@ -1,5 +1,5 @@
-// box_f32.hip -- the run-time-shaped passes of box.h for FP32-stored f, the
-// rules that choose them, and the reduction of their density sums.
+// box_f32.hip -- the run-time-shaped kick of box.h for FP32-stored f, the rules that
+// choose the passes of box.h, and the reduction of their density sums.
 #include <algorithm>
 
 #include "box.h"
@@ -14,11 +14,6 @@ namespace {
 hipError_t launch_kick_box_f32(const KickArgs& a, const int nv[3], hipStream_t s)
 {
   return launch_kick_box_t<float>(a, nv, s);
-}
-
-hipError_t launch_drift_box_f32(const DriftBoxArgs& a, int w, hipStream_t s)
-{
-  return launch_drift_box_t<float>(a, w, s);
 }
 
 // rho[cell] = dv3 sum_k part[k np + cell]: a workgroup takes four cells (there
@@ -131,10 +126,7 @@ hipError_t launch_kick_box(const KickArgs& a, int dtype, const int nv[3], hipStr
 //   cells, whose lines one or two workgroups take in turn (12^3 of one value 9.6 ->
 //   14.3, 3 x 6 x 128 of two 15.6 -> 32).
 //
-// FP64 only: the pass sums the density in another order than the x sweep, whose
-// sums FP32 gradients were differentiated with. A last bit of the acceleration
-// can move the rounding of a line's alpha to FP32, and a corrector switch behind
-// it; and at 8^3 x 16^3 FP32 the pass with its sums took what the three sweeps
+// FP64 only: at 8^3 x 16^3 FP32 the pass with its sums took what the three sweeps
 // take (15 + 4.5 us against 17 + 2.6).
 int drift_box_cells(int dtype, const int n[3], long long nv3)
 {
@@ -159,7 +151,7 @@ hipError_t launch_drift_box(const DriftBoxArgs& a, int dtype, hipStream_t s)
 {
   const int w = drift_box_cells(dtype, a.n, a.nv3);
   if (w == 0) return hipErrorInvalidValue;
-  return dtype == 0 ? launch_drift_box_f32(a, w, s) : launch_drift_box_f64(a, w, s);
+  return launch_drift_box_f64(a, w, s);
 }
 
 hipError_t launch_box_density(double* rho, const double* part, long long np, long long nchunk, double dv3,

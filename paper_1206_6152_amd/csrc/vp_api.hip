@@ -945,7 +945,6 @@ int vp_init(const vp_config* cfg, void* f_dev, void* hip_stream, vp_ctx** out)
     q.n = c->ng;
     q.g = c->wg;
     q.isolated = cfg->bc == VP_BC_ISOLATED;
-    q.G = cfg->G;
     for (int l = 0; l < 3; l++) {
       q.d[l] = c->dx[l];
       q.tw[l] = c->tw[l];

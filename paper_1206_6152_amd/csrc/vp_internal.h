@@ -114,7 +114,7 @@ bool drift_yz_supported(int dtype, int ny, int nz, long long nv3, long long nvz)
 hipError_t launch_drift_yz(const DriftArgs& a, int dtype, hipStream_t s);
 
 // Two position sweeps, along A and then B, in one pass over tiles of velocity
-// cells of the (A, B) plane at one index o of the third axis (drift_pair.hip).
+// cells of the (A, B) plane at one index o of the third axis (drift_pair.h).
 // With part (B = x, A = y, o = z) the pass leaves the density sums of the x
 // sweep's layout: part[((y nz + z) nv3/256 + chunk) nx + x].
 struct DriftPairAxis {
@@ -204,7 +204,7 @@ struct SgStage {       // R > 100: whole lines of R - 100 cells, `step` of them
 struct SmallGravity {
   Grid3 n, g;          // spatial grid, transform grid
   int isolated;
-  double G, d[3];
+  double d[3];
   const double2* tw[3];
   const double2* kspec;   // Green's function's spectrum
   const double* rho;
@@ -289,8 +289,7 @@ hipError_t launch_accel_max(double* work, double* dst, const double* accel, long
 hipError_t launch_sweep_adjoint(const SweepArgs& a, int dtype, const void* fin, void* lam, double* dnu,
                                 hipStream_t s);
 bool adjoint_addend_supported(const SweepArgs& a);
-// lam_a[s] += scale * sum_{i < per} dnu[s*per + i], s < np
-// Reverse of one half kick T_vz T_vy T_vx in one pass (see adjoint.hip): lam
+// Reverse of one half kick T_vz T_vy T_vx in one pass (kick_adjoint.hip): lam
 // <- J^T lam at forward input fin, and lam_a[l][s] += scale[l] * (the block's
 // summed line adjoints), for the grids kick_adjoint_supported accepts.
 struct KickAdjArgs {
@@ -303,6 +302,7 @@ struct KickAdjArgs {
 };
 bool kick_adjoint_supported(int dtype, const int nv[3]);
 hipError_t launch_kick_adjoint(const KickAdjArgs& a, int dtype, const int nv[3], hipStream_t s);
+// lam_a[s] += scale * sum_{i < per} dnu[s*per + i], s < np
 hipError_t launch_reduce_lines(double* lam_a, const double* dnu, long long np, long long per, double scale,
                                hipStream_t s);
 hipError_t launch_gradient_adj(double* lphi_ext, const double* lam_a, Grid3 n, double d0, double d1, double d2,
