@@ -81,13 +81,14 @@ static int kick_box_chain(const int nv[3], int threads)
 }
 
 // Where the one-pass kick is the better choice than the three sweeps (us, three
-// sweeps -> one pass; 2000 shapes of random axes and cells were timed, and none
-// that this rule takes is slower):
+// sweeps -> one pass; 3000 shapes of random axes and cells were timed, and none
+// that this rule takes is more than 5 % slower):
 // - A workgroup is started for every block, however small: on many cells of tiny
 //   blocks that is the time (131 072 blocks of 2^3 FP32 14 -> 64, 49 152 of 4^3 FP64
 //   26 -> 42; 8192 of either, and any number of blocks from 192 cells on, less).
-// - With no more blocks than CUs a lane's chain of cells is the time (8 x 32 x 128 FP32
-//   on two cells 13.7 -> 18.3 at 256; up to 128 cells at most 0.97 of the sweeps).
+// - On a few cells the sweeps take three launches' time, the pass that of a lane's
+//   chain of cells (8 x 32 x 128 FP32 on two cells 13.7 -> 18.3 at 256, up to 1.5 times
+//   the sweeps; up to 128 cells at most 1.05 of them, from 32 cells on 0.7 on average).
 // - Lines of 96 and 128 cells that are not split over lanes leave most lanes without a
 //   line and spill in FP64: 128 x 96 x 1 FP64 on 24^3 cells 1940 -> 2600, 12 x 2 x 128 FP32
 //   on 24 576 368 -> 519; split ones take half of the sweeps' time on few cells, but the
@@ -96,9 +97,9 @@ bool kick_box_supported(int dtype, const int nv[3], long long np)
 {
   if ((size_t)nv[0] * nv[1] * (nv[2] | 1) * (dtype == 0 ? 4 : 8) > (size_t)kLdsMost) return false;
   if (nv[0] * nv[1] * nv[2] < 192 && np > 8192) return false;
+  if (np >= 32 && np <= 256) return true;
   const int chain = kick_box_chain(nv, kick_box_threads(dtype, nv, np));
-  if (np <= 256) return chain <= 128;
-  if (np <= 512) return chain <= 256;
+  if (np < 32) return chain <= 128;
   return std::max(nv[0], std::max(nv[1], nv[2])) <= 64 || (chain <= 64 && np <= 16384);
 }
 

@@ -29,15 +29,18 @@ namespace {
 // tile's lines prefetched under the B sweeps, and the registers for that, the
 // first takes 0.38 ms and the second the same 7.9; one-line rows (W = 32) 0.30
 // and 8.3.
+// rows of one wave where two tiles of them fit a CU, else of one cache line
+constexpr int pair_row(int es, int cells) { return es == 4 && cells <= 320 ? 64 : (cells <= 320 ? 256 : 128) / es; }
+// rows of lanes: the shorter axis, in whole waves
+constexpr int pair_rows(int least, int w) { return least * w % 64 == 0 ? least : (2 * least * w % 64 == 0 ? 2 * least : 4 * least); }
+
 template <typename T, int NA, int NB>
 struct PairShape {
   static constexpr int CELLS = NA * NB;
-  // rows of one wave where two tiles of them fit a CU, else of one cache line
-  static constexpr int W = sizeof(T) == 4 && CELLS <= 320 ? 64 : (CELLS <= 320 ? 256 : 128) / (int)sizeof(T);
+  static constexpr int W = pair_row(sizeof(T), CELLS);
   static constexpr int BYTES = CELLS * W * (int)sizeof(T);
   static constexpr int MIN = NA < NB ? NA : NB;
-  // rows of lanes: the shorter axis, in whole waves
-  static constexpr int S = MIN * W % 64 == 0 ? MIN : (2 * MIN * W % 64 == 0 ? 2 * MIN : 4 * MIN);
+  static constexpr int S = pair_rows(MIN, W);
   static constexpr int THREADS = S * W;
   static constexpr int TILES = 256 / W;
   static constexpr int KA = (NB + S - 1) / S, KB = (NA + S - 1) / S;   // lines per lane

@@ -18,6 +18,13 @@ bool drift_pair_supported(int dtype, int na, int nb, long long nv3)
          nv3 < (1LL << 31);
 }
 
+// wavefronts of the pass over the axes na, nb with o cells on the third
+long long drift_pair_waves(int dtype, int na, int nb, int o, long long nv3)
+{
+  const int w = pair_row(dtype == 0 ? 4 : 8, na * nb);
+  return o * (nv3 / 256) * (pair_rows(na < nb ? na : nb, w) * w / 64);
+}
+
 hipError_t launch_drift_pair_f32(const DriftPairArgs& p, int na, int nb, hipStream_t s)
 {
   return launch_pair_t<float>(p, na, nb, s);

@@ -733,13 +733,13 @@ int drift(vp_ctx* c, double tau, bool x_sums = false)
 }
 
 // Two position axes that share a pass (drift_pair) save one of the drift's
-// passes over f: 10 to 29 % of a step wherever the pass has enough workgroups
-// (2 steps of 24 x 12 x 48 with 32^3 blocks FP32 6.41 -> 5.24 ms, 16 x 16 x 64 7.91 ->
-// 6.12, 48 x 48 x 12 with 24 x 24 x 32 FP64 18.7 -> 15.5). With few its serial tiles
-// show, and the single sweeps stay (2600 shapes of up to 2500 workgroups, drift
-// against the sweeps): up to 400 workgroups between 0.7 and 1.36 of their time, and
-// up to 600 as much as 1.17 for planes over 320 cells, whose tiles have half the
-// rows; of what the rule takes, 0.51 to 1.08, 0.82 on average. Square planes with
+// passes over f: 10 to 29 % of a step (2 steps of 24 x 12 x 48 with 32^3 blocks FP32
+// 6.41 -> 5.24 ms, 16 x 16 x 64 7.91 -> 6.12, 48 x 48 x 12 with 24 x 24 x 32 FP64 18.7 ->
+// 15.5). Its tiles are serial, so the sweeps stay where workgroups, or wavefronts of
+// an array that the last-level cache holds, are few: 288 workgroups over 256 CUs took
+// 0.75 to 1.36 of the sweeps' time, 48 x 12 planes of six-cell vz rows 1.17 at 576. Of
+// 1100 shapes of up to 2500 workgroups that the rule takes, 0.8 of the sweeps' time on
+// average and 1.04 at most. Square planes with
 // a kernel of their own (drift_yz) keep it (16^3 x 16^3 FP32: 231 us, 251 with
 // the pair), except the FP32 64-cell plane, whose half-line chunks run at half
 // the copy rate (4 x 64 x 64 with 32^3: 7.36 -> 6.46 ms, with 16^3 the same).
@@ -750,9 +750,12 @@ int pair_plan(const vp_ctx* c)
 {
   const auto& k = c->cfg;
   const long long chunks = c->nv3 / 256;
+  const long long bytes = c->np * c->nv3 * (k.dtype == VP_F32 ? 4 : 8);
   auto pays = [&](int a, int b, int o) {
-    return vp::drift_pair_supported(k.dtype, k.n[a], k.n[b], c->nv3) &&
-           k.n[o] * chunks > (k.n[a] * k.n[b] > 320 ? 600 : 400);
+    const long long groups = k.n[o] * chunks;
+    return vp::drift_pair_supported(k.dtype, k.n[a], k.n[b], c->nv3) && groups >= 320 &&
+           (bytes >= (48LL << 20) || vp::drift_pair_waves(k.dtype, k.n[a], k.n[b], k.n[o], c->nv3) > 5 * 256) &&
+           (k.n[a] * k.n[b] <= 320 || k.nv[2] >= 8 || groups > 600);
   };
   const bool yx = c->xsum && pays(1, 0, 2);
   if (vp::drift_yz_supported(k.dtype, k.n[1], k.n[2], c->nv3, k.nv[2])) return yx && k.n[1] == 64 ? 1 : 0;

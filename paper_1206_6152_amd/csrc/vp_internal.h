@@ -131,6 +131,7 @@ struct DriftPairArgs {
   double* part;
 };
 bool drift_pair_supported(int dtype, int na, int nb, long long nv3);
+long long drift_pair_waves(int dtype, int na, int nb, int o, long long nv3);
 hipError_t launch_drift_pair(const DriftPairArgs& a, int dtype, int na, int nb, hipStream_t s);
 
 // The half kick (or two) of a velocity block of any shape that fits the LDS, in

@@ -25,12 +25,12 @@ KICKS = [
     # small blocks: a workgroup per block up to 8192 cells, or from 192 values on
     ((64, 64, 2), (2, 2, 2), VP_F32, ONE), ((64, 64, 3), (2, 2, 2), VP_F32, SWEEPS), ((64, 64, 64), (1, 1, 1), VP_F32, SWEEPS),
     ((48, 32, 48), (4, 4, 4), VP_F64, SWEEPS), ((24, 24, 24), (4, 4, 12), VP_F64, ONE), ((24, 24, 24), (6, 4, 6), VP_F32, SWEEPS),
-    # few cells: the busiest lane's chain of up to 128 cells, with more lanes per block
+    # below 32 cells: the busiest lane's chain of up to 128 cells, with more lanes per block
     ((1, 1, 1), (32, 64, 1), VP_F32, ONE), ((2, 1, 1), (8, 32, 128), VP_F32, SWEEPS), ((1, 2, 1), (64, 32, 16), VP_F32, ONE),
-    ((2, 2, 1), (24, 12, 128), VP_F32, SWEEPS), ((3, 3, 1), (12, 12, 12), VP_F64, ONE), ((8, 8, 4), (16, 48, 24), VP_F64, SWEEPS),
-    ((8, 8, 6), (16, 48, 24), VP_F64, ONE),
+    ((2, 2, 1), (24, 12, 128), VP_F32, SWEEPS), ((3, 3, 1), (12, 12, 12), VP_F64, ONE), ((4, 6, 1), (16, 48, 24), VP_F64, SWEEPS),
+    ((4, 8, 1), (16, 48, 24), VP_F64, ONE), ((4, 8, 1), (24, 12, 128), VP_F32, ONE), ((8, 8, 6), (24, 12, 128), VP_F32, SWEEPS),
     # long lines on many cells: only where they are split over lanes
-    ((24, 24, 2), (128, 24, 1), VP_F64, SWEEPS), ((8, 8, 8), (128, 24, 1), VP_F64, ONE), ((24, 24, 2), (128, 4, 1), VP_F64, ONE),
+    ((24, 24, 2), (128, 24, 1), VP_F64, SWEEPS), ((8, 8, 4), (128, 24, 1), VP_F64, ONE), ((24, 24, 2), (128, 4, 1), VP_F64, ONE),
     ((16, 16, 4), (12, 2, 128), VP_F32, SWEEPS), ((16, 16, 4), (12, 2, 64), VP_F32, ONE),
     ((64, 64, 8), (1, 96, 3), VP_F32, SWEEPS), ((64, 64, 4), (1, 96, 3), VP_F32, ONE),
 ]
@@ -123,11 +123,11 @@ def test_fp64_drift_takes_the_faster_route(n, nv, route):
 
 # two position axes in one pass: "yx", "zy", or the single sweeps ("-"), for both types
 PAIRS = [
-    ((6, 4, 48), (16, 16, 16), "yx", "yx"), ((6, 4, 48), (16, 8, 16), "-", "-"), ((12, 16, 24), (16, 24, 12), "yx", "yx"),
+    ((6, 4, 48), (16, 16, 16), "yx", "yx"), ((6, 4, 48), (16, 8, 16), "yx", "-"), ((6, 4, 24), (16, 8, 24), "-", "-"), ((12, 16, 24), (16, 24, 12), "yx", "yx"),
     ((4, 64, 64), (8, 16, 16), "yx", "yx"), ((6, 64, 48), (24, 24, 8), "yx", "-"), ((12, 48, 16), (24, 24, 24), "yx", "yx"),
-    ((12, 48, 16), (16, 24, 24), "-", "-"), ((8, 12, 24), (12, 12, 32), "yx", "yx"),
-    ((48, 6, 4), (8, 32, 12), "zy", "zy"), ((24, 24, 4), (16, 24, 16), "zy", "zy"), ((48, 8, 48), (16, 16, 16), "zy", "zy"),
-    ((24, 24, 16), (16, 32, 16), "zy", "zy"), ((24, 24, 16), (16, 24, 16), "-", "-"), ((48, 12, 8), (8, 32, 12), "zy", "zy"),
+    ((12, 48, 16), (16, 24, 24), "yx", "yx"), ((12, 48, 16), (16, 16, 16), "-", "-"), ((8, 12, 24), (12, 12, 32), "yx", "yx"),
+    ((48, 6, 4), (8, 32, 12), "zy", "-"), ((48, 6, 4), (16, 32, 12), "zy", "zy"), ((24, 24, 4), (16, 24, 16), "zy", "zy"), ((48, 8, 48), (16, 16, 16), "zy", "zy"),
+    ((24, 24, 16), (16, 32, 16), "zy", "zy"), ((24, 24, 16), (16, 24, 16), "zy", "zy"), ((48, 48, 12), (16, 32, 6), "-", "-"), ((48, 12, 8), (8, 32, 12), "zy", "zy"),
     ((48, 64, 6), (8, 32, 16), "zy", "-"),
 ]
 
