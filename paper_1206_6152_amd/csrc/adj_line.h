@@ -35,8 +35,10 @@ __device__ __forceinline__ AdjCoef<T> adj_coef(double nu, bool periodic)
 // sends its own terms to out_i, its Lp interior-branch term to out_{i+1} and
 // its Lm interior-branch term to out_{i-1}, so out_{i-1} is written once cell i
 // is known. Every rounding step is written out, so all kernels agree bit for
-// bit. 29 vector instructions per cell; a pass of its own for alpha's adjoint
-// and a product per term took 41.
+// bit. 36 vector instructions per FP32 cell with alpha's adjoint, seven less without;
+// a pass of its own for alpha's adjoint and a product per term took 41. Products
+// merged per line (c1 alpha and the like) would leave 29, but other roundings: FP32
+// gradients moved by up to 6e-9.
 template <typename T, int N, bool ALPHA = true>
 __device__ __forceinline__ void adj_core(const T (&w)[N], T (&l)[N], T finf, const AdjCoef<T>& k, bool periodic,
                                          T& lfinf, T& lalpha)

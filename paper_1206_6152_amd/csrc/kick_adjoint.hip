@@ -26,9 +26,11 @@ namespace {
 // coefficients are worked out once per block (three lanes, while the first
 // loads are in flight), and each axis is held in LDS in the orientation of its
 // motion, so that the updates need no selects for the direction and a
-// whole-cell shift is a uniform branch. Bound by vector issue: 16^3 x 24^3 FP32
-// takes 0.39 ms instead of 0.50. The per-line results are the same bits as those of the single
-// reverse sweeps, and the nu adjoints are added per axis in the order of
+// whole-cell shift is a uniform branch. 16^3 x 24^3 FP32 takes 0.376 ms instead of
+// 0.50. The vector units are busy for 0.62 of that (162 instructions per cell for six
+// sweeps); what is left are the loads and LDS accesses between the barriers, which
+// two workgroups on a CU hide in part. The per-line results are the same bits as those
+// of the single reverse sweeps, and the nu adjoints are added per axis in the order of
 // reduce_lines_kernel.
 template <typename T, int N>
 struct AdjKickShape {
