@@ -25,6 +25,13 @@ long long drift_pair_waves(int dtype, int na, int nb, int o, long long nv3)
   return o * (nv3 / 256) * (pair_rows(na < nb ? na : nb, w) * w / 64);
 }
 
+// bytes of LDS a workgroup of it holds
+int drift_pair_tile(int dtype, int na, int nb)
+{
+  const int es = dtype == 0 ? 4 : 8;
+  return na * nb * pair_row(es, na * nb) * es;
+}
+
 hipError_t launch_drift_pair_f32(const DriftPairArgs& p, int na, int nb, hipStream_t s)
 {
   return launch_pair_t<float>(p, na, nb, s);

@@ -738,8 +738,13 @@ int drift(vp_ctx* c, double tau, bool x_sums = false)
 // 15.5). Its tiles are serial, so the sweeps stay where workgroups, or wavefronts of
 // an array that the last-level cache holds, are few: 288 workgroups over 256 CUs took
 // 0.75 to 1.36 of the sweeps' time, 48 x 12 planes of six-cell vz rows 1.17 at 576. Of
-// 1100 shapes of up to 2500 workgroups that the rule takes, 0.8 of the sweeps' time on
-// average and 1.04 at most. Square planes with
+// 2900 shapes of up to 2500 workgroups, those that the rule takes have 0.8 of the sweeps'
+// time on average and 1.08 at most. The short z lines of FP32 planes of 6 or 12 x 48 cells stay
+// too where their vz rows are shorter than 32 cells: a wavefront reads runs of half
+// a vz row, as opposite velocities read their lines from opposite ends, and tiles
+// of 72 KiB and six wavefronts, two to a CU, hide nothing of runs under 64 bytes (122
+// shapes: 0.85 to 1.21 of the sweeps' time, 1.00 on average; 75 of longer rows 0.72 to
+// 0.98, and 0.82). Square planes with
 // a kernel of their own (drift_yz) keep it (16^3 x 16^3 FP32: 231 us, 251 with
 // the pair), except the FP32 64-cell plane, whose half-line chunks run at half
 // the copy rate (4 x 64 x 64 with 32^3: 7.36 -> 6.46 ms, with 16^3 the same).
@@ -751,11 +756,15 @@ int pair_plan(const vp_ctx* c)
   const auto& k = c->cfg;
   const long long chunks = c->nv3 / 256;
   const long long bytes = c->np * c->nv3 * (k.dtype == VP_F32 ? 4 : 8);
+  auto thin = [&](int a, int b) {
+    return k.dtype == VP_F32 && a == 2 && k.nv[2] < 32 && k.n[2] < k.n[1] && vp::drift_pair_tile(k.dtype, k.n[2], k.n[1]) > 64 * 1024 &&
+           vp::drift_pair_waves(k.dtype, k.n[2], k.n[1], 1, 256) <= 6;
+  };
   auto pays = [&](int a, int b, int o) {
     const long long groups = k.n[o] * chunks;
     return vp::drift_pair_supported(k.dtype, k.n[a], k.n[b], c->nv3) && groups >= 320 &&
            (bytes >= (48LL << 20) || vp::drift_pair_waves(k.dtype, k.n[a], k.n[b], k.n[o], c->nv3) > 5 * 256) &&
-           (k.n[a] * k.n[b] <= 320 || k.nv[2] >= 8 || groups > 600);
+           (k.n[a] * k.n[b] <= 320 || k.nv[2] >= 8 || groups > 600) && !thin(a, b);
   };
   const bool yx = c->xsum && pays(1, 0, 2);
   if (vp::drift_yz_supported(k.dtype, k.n[1], k.n[2], c->nv3, k.nv[2])) return yx && k.n[1] == 64 ? 1 : 0;

@@ -132,6 +132,7 @@ struct DriftPairArgs {
 };
 bool drift_pair_supported(int dtype, int na, int nb, long long nv3);
 long long drift_pair_waves(int dtype, int na, int nb, int o, long long nv3);
+int drift_pair_tile(int dtype, int na, int nb);
 hipError_t launch_drift_pair(const DriftPairArgs& a, int dtype, int na, int nb, hipStream_t s);
 
 // The half kick (or two) of a velocity block of any shape that fits the LDS, in

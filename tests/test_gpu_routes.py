@@ -129,6 +129,10 @@ PAIRS = [
     ((48, 6, 4), (8, 32, 12), "zy", "-"), ((48, 6, 4), (16, 32, 12), "zy", "zy"), ((24, 24, 4), (16, 24, 16), "zy", "zy"), ((48, 8, 48), (16, 16, 16), "zy", "zy"),
     ((24, 24, 16), (16, 32, 16), "zy", "zy"), ((24, 24, 16), (16, 24, 16), "zy", "zy"), ((48, 48, 12), (16, 32, 6), "-", "-"), ((48, 12, 8), (8, 32, 12), "zy", "zy"),
     ((48, 64, 6), (8, 32, 16), "zy", "-"),
+    # short z lines beside long y ones, by the length of a vz row
+    ((48, 48, 6), (8, 16, 24), "-", "zy"), ((48, 48, 6), (8, 8, 32), "zy", "zy"), ((32, 48, 12), (12, 24, 16), "-", "zy"),
+    ((32, 48, 12), (6, 24, 32), "zy", "zy"), ((6, 48, 6), (24, 24, 24), "yx", "zy"), ((48, 6, 48), (16, 8, 24), "zy", "zy"),
+    ((48, 6, 48), (8, 8, 24), "-", "-"),
 ]
 
 
